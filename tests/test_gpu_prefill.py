@@ -187,3 +187,40 @@ def test_item_rounds_with_a_partial_last_round(gpu_lib, chunks, hq, hkv):
     err = float(np.abs(got[rows] - ref[rows]).max())
     note(f"  max abs err {err:.3e}")
     assert np.isfinite(got).all() and err <= TOL["bf16"]
+
+
+def _edges(qs):
+    """First, last and 16-row boundary rows of every chunk."""
+    rows = set()
+    for a, b in zip(qs[:-1], qs[1:]):
+        rows |= {int(r) for r in (a, b - 1, a + 15, a + 16, (a + b) // 2) if a <= r < b}
+    return sorted(rows)
+
+
+@pytest.mark.parametrize("chunks,hq,hkv,kv", [
+    # items of 64 columns: one-column remainders, contexts at the ends of 32-token tiles
+    ([(1, 1), (16, 16), (17, 33), (8, 64), (15, 95), (31, 96), (33, 97)], 8, 2, "bf16"),
+    ([(3, 31), (4, 32), (5, 33), (9, 160)], 16, 1, "fp8_e4m3"),
+    # 128 columns, two waves on halves of the context: odd and even tile counts, chunks that end in either half
+    ([(7, 2100), (33, 2049), (40, 40), (1, 33), (2, 64), (3, 65)], 16, 2, "bf16"),
+    ([(7, 2100), (33, 2081), (16, 32), (17, 97)], 16, 1, "fp8_e4m3"),
+    # 128 columns, four waves: GQA 4 and 5 (columns that cross tokens)
+    ([(700, 700), (333, 500), (301, 301)], 32, 8, "bf16"),
+    ([(701, 800), (333, 333), (1, 1)], 40, 8, "fp8_e4m3"),
+    # 256 columns: GQA 5, a remainder of one token
+    ([(1001, 1333), (97, 97), (1, 700)], 60, 12, "bf16"),
+    # more sequences than a wave has lanes, more rounds of items than are looked up at once
+    ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16"),
+])
+def test_item_widths(gpu_lib, chunks, hq, hkv, kv):
+    """Each width of work item the library chooses between, at the ends of its
+    tiles and columns; every row is written, edge rows match the oracle."""
+    note(f"prefill widths {len(chunks)} chunks {hq}/{hkv} {kv}")
+    w = workloads.make_prefill(chunks, hq, hkv, c_max=max(t for _, t in chunks), kv_format=kv, seed=31)
+    rows = _edges(w.meta["q_start"])
+    rows = rows[:: max(1, len(rows) // 60)]
+    got = gpu_rows(gpu_lib, w)
+    ref = oracle_rows(w, rows)
+    err = float(np.abs(got[rows] - ref[rows]).max())
+    note(f"  max abs err {err:.3e}")
+    assert np.isfinite(got).all() and err <= TOL[kv]
