@@ -434,10 +434,122 @@ __device__ __forceinline__ int div_small(int a, int d, float rd) {
   return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
+// Per-lane operand offsets inside a tile, and the block of the unit that this
+// lane's K and V fragments come from.
+template <bool FP8>
+__device__ __forceinline__ void lane_offsets(int li, int lj, int (&kofs)[8], int (&vofs)[8], int& kblk, int& vblk) {
+  if constexpr (FP8) {
+    // K: MFMA m (0..3), row li = token 4m + (li & 3) of block li >> 2; fragment j = dims 64j + 16lj .. +16
+    for (int m = 0; m < 4; ++m)
+      for (int jj = 0; jj < 2; ++jj) kofs[2 * m + jj] = (4 * m + (li & 3)) * 128 + 64 * jj + 16 * lj;
+    kblk = li >> 2;
+    // V: dim 16nn + li, all 16 tokens of block lj
+    for (int nn = 0; nn < 8; ++nn) vofs[nn] = (16 * nn + li) * 16;
+    vblk = lj;
+  } else {
+    // K: MFMA m (0..1), row li = token 8((li >> 2) & 1) + 4m + (li & 3) of block li >> 3; chunk c = dims 32c + 8lj
+    for (int m = 0; m < 2; ++m)
+      for (int c = 0; c < 4; ++c) kofs[4 * m + c] = (8 * ((li >> 2) & 1) + 4 * m + (li & 3)) * 256 + 64 * c + 16 * lj;
+    kblk = li >> 3;
+    // V: dim 16nn + li, tokens 8(lj & 1) .. +8 of block lj >> 1
+    for (int nn = 0; nn < 8; ++nn) vofs[nn] = (16 * nn + li) * 32 + 16 * (lj & 1);
+    vblk = lj >> 1;
+  }
+}
+
+// One unit of a piece: scores of the unit's tokens from unit_tok0 on (those at
+// or past ctx_s masked), online softmax, output products.
+template <bool FP8>
+__device__ __forceinline__ void attend_unit(const UnitRegs& R, const i32x4 (&qv)[4], int unit_tok0, int ctx_s, int lj,
+                                            float cscale, float& m_run, float& l_part, f32x4 (&acc)[8]) {
+  constexpr int UT = Geo<FP8>::UT, NZ = Geo<FP8>::NZ;
+  const bool ragged = unit_tok0 + UT > ctx_s;
+  const int lane_tok0 = unit_tok0 + (FP8 ? 16 : 8) * lj;  // first unit token of this lane's scores
+
+  // S^T = K Q^T: lane (li, lj) holds scores of head li for its NZ tokens
+  float z[NZ];
+  if constexpr (FP8) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const i32x4 raw = R.k[2 * m + jj];
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[0], raw[1]),
+                                                       __builtin_bit_cast(bf16x8, qv[2 * jj]), sacc, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[2], raw[3]),
+                                                       __builtin_bit_cast(bf16x8, qv[2 * jj + 1]), sacc, 0, 0,
+                                                       0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[4 * m + e] = sacc[e] * cscale;
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, R.k[4 * m + c]),
+                                                       __builtin_bit_cast(bf16x8, qv[c]), sacc, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[4 * m + e] = sacc[e] * cscale;
+    }
+  }
+  // live tokens among this lane's NZ tokens (all of them unless the unit is ragged)
+  const int nv = ragged ? min(max(ctx_s - lane_tok0, 0), NZ) : NZ;
+  if (ragged)
+#pragma unroll
+    for (int e = 0; e < NZ; ++e)
+      if (e >= nv) z[e] = -INFINITY;
+
+  // online softmax (base 2) for head li over this unit's tokens
+  float bmax = z[0];
+  for (int e = 1; e < NZ; ++e) bmax = fmaxf(bmax, z[e]);
+  bmax = xor_max(bmax);
+  const float m_new = fmaxf(m_run, bmax);
+  if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {  // some head's max grew: rescale
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    l_part *= alpha;
+#pragma unroll
+    for (int nn = 0; nn < 8; ++nn) acc[nn] *= alpha;
+    m_run = m_new;
+  }
+  bf16x8 p[NZ / 8];
+  float psum = 0.f;
+#pragma unroll
+  for (int e = 0; e < NZ; ++e) {
+    const __bf16 pe = (__bf16)__builtin_amdgcn_exp2f(z[e] - m_run);
+    p[e >> 3][e & 7] = pe;
+    psum += (float)pe;
+  }
+  l_part += psum;
+
+  // O^T += V^T P^T.  A V fragment is 16 bytes: 8 bf16 tokens, or 16 fp8
+  // tokens (8 for each of two MFMAs); dead tokens are zeroed on the raw words.
+  unsigned vmask[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+  if (ragged)
+#pragma unroll
+    for (int wd = 0; wd < 4; ++wd) vmask[wd] = live_mask<FP8 ? 1 : 2>(wd, nv);
+#pragma unroll
+  for (int nn = 0; nn < 8; ++nn) {
+    i32x4 raw = R.v[nn];
+    if (ragged)
+#pragma unroll
+      for (int wd = 0; wd < 4; ++wd) raw[wd] &= (int)vmask[wd];
+    if constexpr (FP8) {
+      acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[0], raw[1]), p[0], acc[nn], 0, 0, 0);
+      acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[2], raw[3]), p[1], acc[nn], 0, 0, 0);
+    } else {
+      acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), p[0], acc[nn], 0, 0, 0);
+    }
+  }
+}
+
 template <bool FP8>
 __global__ __launch_bounds__(kWaves * 64) void paged_decode_kernel(DecodeArgs a) {
   using GE = Geo<FP8>;
-  constexpr int UB = GE::UB, UT = GE::UT, TILE = GE::TILE, NZ = GE::NZ;
+  constexpr int UB = GE::UB, UT = GE::UT, TILE = GE::TILE;
   __shared__ int tiles_lds[kWaves][kMaxUnitsPerWave * UB];
   __shared__ int wave_sums[kWaves];
   // Split pieces are first merged inside the workgroup: the segment (s, g)
@@ -459,23 +571,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_kernel(DecodeArgs a)
   // ---- per-lane operand offsets inside a tile ----
   int kofs[8], vofs[8];
   int kblk, vblk;  // which block of the unit this lane's K / V fragments come from
-  if constexpr (FP8) {
-    // K: MFMA m (0..3), row li = token 4m + (li & 3) of block li >> 2; fragment j = dims 64j + 16lj .. +16
-    for (int m = 0; m < 4; ++m)
-      for (int jj = 0; jj < 2; ++jj) kofs[2 * m + jj] = (4 * m + (li & 3)) * 128 + 64 * jj + 16 * lj;
-    kblk = li >> 2;
-    // V: dim 16nn + li, all 16 tokens of block lj
-    for (int nn = 0; nn < 8; ++nn) vofs[nn] = (16 * nn + li) * 16;
-    vblk = lj;
-  } else {
-    // K: MFMA m (0..1), row li = token 8((li >> 2) & 1) + 4m + (li & 3) of block li >> 3; chunk c = dims 32c + 8lj
-    for (int m = 0; m < 2; ++m)
-      for (int c = 0; c < 4; ++c) kofs[4 * m + c] = (8 * ((li >> 2) & 1) + 4 * m + (li & 3)) * 256 + 64 * c + 16 * lj;
-    kblk = li >> 3;
-    // V: dim 16nn + li, tokens 8(lj & 1) .. +8 of block lj >> 1
-    for (int nn = 0; nn < 8; ++nn) vofs[nn] = (16 * nn + li) * 32 + 16 * (lj & 1);
-    vblk = lj >> 1;
-  }
+  lane_offsets<FP8>(li, lj, kofs, vofs, kblk, vblk);
   auto issue_at = [&](UnitRegs& R, int kt, int vt) __attribute__((always_inline)) {
     const char* kb = a.k + (size_t)kt * TILE;
     const char* vb = a.v + (size_t)vt * TILE;
@@ -707,88 +803,7 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_kernel(DecodeArgs a)
     };
 
     auto compute_unit = [&](const UnitRegs& R) __attribute__((always_inline)) {
-      const int unit_tok0 = cs.j * UT;
-      const bool ragged = unit_tok0 + UT > ctx_s;
-      const int lane_tok0 = unit_tok0 + (FP8 ? 16 : 8) * lj;  // first unit token of this lane's scores
-
-      // S^T = K Q^T: lane (li, lj) holds scores of head li for its NZ tokens
-      float z[NZ];
-      if constexpr (FP8) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            const i32x4 raw = R.k[2 * m + jj];
-            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[0], raw[1]),
-                                                           __builtin_bit_cast(bf16x8, qv[2 * jj]), sacc, 0, 0, 0);
-            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[2], raw[3]),
-                                                           __builtin_bit_cast(bf16x8, qv[2 * jj + 1]), sacc, 0, 0,
-                                                           0);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) z[4 * m + e] = sacc[e] * cscale;
-        }
-      } else {
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, R.k[4 * m + c]),
-                                                           __builtin_bit_cast(bf16x8, qv[c]), sacc, 0, 0, 0);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) z[4 * m + e] = sacc[e] * cscale;
-        }
-      }
-      // live tokens among this lane's NZ tokens (all of them unless the unit is ragged)
-      const int nv = ragged ? min(max(ctx_s - lane_tok0, 0), NZ) : NZ;
-      if (ragged)
-#pragma unroll
-        for (int e = 0; e < NZ; ++e)
-          if (e >= nv) z[e] = -INFINITY;
-
-      // online softmax (base 2) for head li over this unit's tokens
-      float bmax = z[0];
-      for (int e = 1; e < NZ; ++e) bmax = fmaxf(bmax, z[e]);
-      bmax = xor_max(bmax);
-      const float m_new = fmaxf(m_run, bmax);
-      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {  // some head's max grew: rescale
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        l_part *= alpha;
-#pragma unroll
-        for (int nn = 0; nn < 8; ++nn) acc[nn] *= alpha;
-        m_run = m_new;
-      }
-      bf16x8 p[NZ / 8];
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < NZ; ++e) {
-        const __bf16 pe = (__bf16)__builtin_amdgcn_exp2f(z[e] - m_run);
-        p[e >> 3][e & 7] = pe;
-        psum += (float)pe;
-      }
-      l_part += psum;
-
-      // O^T += V^T P^T.  A V fragment is 16 bytes: 8 bf16 tokens, or 16 fp8
-      // tokens (8 for each of two MFMAs); dead tokens are zeroed on the raw words.
-      unsigned vmask[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-      if (ragged)
-#pragma unroll
-        for (int wd = 0; wd < 4; ++wd) vmask[wd] = live_mask<FP8 ? 1 : 2>(wd, nv);
-#pragma unroll
-      for (int nn = 0; nn < 8; ++nn) {
-        i32x4 raw = R.v[nn];
-        if (ragged)
-#pragma unroll
-          for (int wd = 0; wd < 4; ++wd) raw[wd] &= (int)vmask[wd];
-        if constexpr (FP8) {
-          acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[0], raw[1]), p[0], acc[nn], 0, 0, 0);
-          acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp8x8_to_bf16(raw[2], raw[3]), p[1], acc[nn], 0, 0, 0);
-        } else {
-          acc[nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), p[0], acc[nn], 0, 0, 0);
-        }
-      }
+      attend_unit<FP8>(R, qv, cs.j * UT, ctx_s, lj, cscale, m_run, l_part, acc);
     };
 
     // End of a piece: its rows (whole segment) or its partial record.
@@ -1109,6 +1124,131 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_kernel(DecodeArgs a)
 template __global__ void paged_decode_kernel<false>(DecodeArgs);
 template __global__ void paged_decode_kernel<true>(DecodeArgs);
 
+// Small calls: one workgroup per segment, no cut segments, no workspace.
+//
+// What bounds a call of a few short sequences is the chain of dependent loads
+// and exchanges, not bytes.  Here the chain is short: the sequence is known
+// from the workgroup's index, so context length, block ids and queries are
+// loaded at once, then K and V, and the waves' sums meet in LDS.  Each of the
+// eight waves has at most two of the segment's units, so all of its loads are
+// in flight together.  A whole segment comes through one compute unit, which
+// takes about 3 us for sixteen units: beyond that, or with more segments than
+// compute units, cut segments are quicker (one layer, us, cut / here: 4
+// sequences of up to 512 tokens on 8/2 heads 10.9 / 9.4; 3 on 64/8 11.7 /
+// 10.4; 32 on 64/8, 256 segments, 15.1 / 14.6, but 64, 512 segments, 20.0 /
+// 24.9; 8 of up to 1,024 tokens, 32 units, 13.3 / 19.2).
+constexpr int kSmallWaves = 8;
+constexpr int kSmallUnits = 2 * kSmallWaves;
+
+template <bool FP8>
+__global__ __launch_bounds__(kSmallWaves * 64) void paged_decode_small_kernel(DecodeArgs a) {
+  using GE = Geo<FP8>;
+  constexpr int UB = GE::UB, UT = GE::UT, TILE = GE::TILE;
+  __shared__ __attribute__((aligned(16))) char rec[kSmallWaves][kRecBytes];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lj = lane >> 4;
+  const int Hkv = a.hkv, G = a.group;
+  const int s = blockIdx.x / Hkv, g = blockIdx.x - s * Hkv;
+  int kofs[8], vofs[8], kblk, vblk;
+  lane_offsets<FP8>(li, lj, kofs, vofs, kblk, vblk);
+  const int ctx = clamp_ctx(a.context_lens[s], a.max_ctx);
+  const int32_t* bt = a.block_tables + (size_t)s * a.max_blocks_per_seq;
+
+  // Block ids of unit u: this lane's K and V blocks and the unit's first,
+  // which stands in for blocks past the sequence's end (never fetched: their
+  // table entries may hold anything).
+  struct Entries { int e0, ek, ev; };
+  auto entries = [&](int u) __attribute__((always_inline)) {
+    const int last = a.max_blocks_per_seq - 1;
+    return Entries{bt[min(u * UB, last)], bt[min(u * UB + kblk, last)], bt[min(u * UB + vblk, last)]};
+  };
+  auto issue = [&](UnitRegs& R, int u, const Entries& e) __attribute__((always_inline)) {
+    const int nb = (ctx + kBlock - 1) / kBlock;
+    const int ik = u * UB + kblk < nb ? e.ek : e.e0, iv = u * UB + vblk < nb ? e.ev : e.e0;
+    const char* kb = a.k + (size_t)(min(max(ik, 0), a.num_blocks_m1) * Hkv + g) * TILE;
+    const char* vb = a.v + (size_t)(min(max(iv, 0), a.num_blocks_m1) * Hkv + g) * TILE;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) R.k[x] = __builtin_nontemporal_load((const i32x4*)(kb + kofs[x]));
+#pragma unroll
+    for (int x = 0; x < 8; ++x) R.v[x] = __builtin_nontemporal_load((const i32x4*)(vb + vofs[x]));
+  };
+  const Entries e0 = entries(w);
+  Entries e1 = entries(w + kSmallWaves);
+  i32x4 qv[4];  // columns past the GQA group repeat a real head
+  {
+    const int qhead = li < G ? li : li % G;
+    const uint16_t* qrow = a.q + ((size_t)s * a.hq + (size_t)g * G + qhead) * kHeadDim;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      qv[c] = *(const i32x4*)(qrow + (FP8 ? 64 * (c >> 1) + 16 * lj + 8 * (c & 1) : 32 * c + 8 * lj));
+  }
+  float cscale = a.qk_scale_log2, vsc = 1.0f;
+  if constexpr (FP8) {
+    cscale *= a.k_scale[g];
+    vsc = a.v_scale[g];
+  }
+  const int nus = units_of<FP8>(ctx);
+  float m_run = -INFINITY, l_part = 0.f;
+  f32x4 acc[8];
+#pragma unroll
+  for (int nn = 0; nn < 8; ++nn) acc[nn] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (w < nus) {
+    const bool two = w + kSmallWaves < nus;
+    if (!two) e1 = e0;
+    UnitRegs R0, R1;
+    issue(R0, w, e0);
+    issue(R1, two ? w + kSmallWaves : w, e1);  // (without a second unit the first again, unused)
+    attend_unit<FP8>(R0, qv, w * UT, ctx, lj, cscale, m_run, l_part, acc);
+    if (two) attend_unit<FP8>(R1, qv, (w + kSmallWaves) * UT, ctx, lj, cscale, m_run, l_part, acc);
+    // this wave's sums: eight 1 KiB chunks of o, then (m, l) per lane
+    const float l_tot = xor_sum(l_part);
+    char* base = rec[w];
+#pragma unroll
+    for (int nn = 0; nn < 8; ++nn) *(f32x4*)(base + nn * 1024 + lane * 16) = acc[nn];
+    float* ml = (float*)(base + 8192 + lane * 8);
+    ml[0] = m_run;
+    ml[1] = l_tot;
+  }
+  lds_barrier();
+  // fold, one (head, 4-value chunk) pair per thread, the waves in order
+  const int p = threadIdx.x;
+  if (p >= G * 32) return;
+  const int hd = p >> 5, d0 = (p & 31) * 4;
+  const int nrec = min(nus, kSmallWaves);
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  if (nrec > 0) {  // (rows of empty sequences are zero)
+    float M = -INFINITY, L = 0.f, m[kSmallWaves];
+#pragma unroll
+    for (int r = 0; r < kSmallWaves; ++r) {
+      m[r] = r < nrec ? *(const float*)(rec[r] + 8192 + hd * 8) : -INFINITY;
+      M = fmaxf(M, m[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallWaves; ++r) {
+      if (r < nrec) {
+        const float wgt = __builtin_amdgcn_exp2f(m[r] - M);
+        const f32x4 x = *(const f32x4*)(rec[r] + (d0 >> 4) * 1024 + (hd + 4 * (d0 & 15)) * 16);
+        o = __builtin_elementwise_fma(x, f32x4{wgt, wgt, wgt, wgt}, o);
+        L = __builtin_fmaf(*(const float*)(rec[r] + 8192 + hd * 8 + 4), wgt, L);
+      }
+    }
+    o *= vsc / L;
+  }
+  const size_t off = ((size_t)s * a.hq + (size_t)g * G + hd) * kHeadDim + d0;
+  if (a.out_fp32) {
+    *(f32x4*)((float*)a.out + off) = o;
+  } else {
+    u16x4 ob;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ob[e] = f32_to_bf16_bits(o[e]);
+    *(u16x4*)((uint16_t*)a.out + off) = ob;
+  }
+}
+
+template __global__ void paged_decode_small_kernel<false>(DecodeArgs);
+template __global__ void paged_decode_small_kernel<true>(DecodeArgs);
+
 // Zero n words (arrival counters).  A kernel rather than a memset, so that a
 // captured graph holds no memset node.
 __global__ __launch_bounds__(256) void zero_words_kernel(int32_t* p, int n) {
@@ -1176,6 +1316,7 @@ struct Plan {
   size_t dyn_lds;   // dynamic LDS bytes
   size_t arrivals_off, rec_ml_off, rec_o_off, tile_cache_off, ws_bytes;
   int clear_words;  // arrival counters to zero before the launch (0 on the usual path)
+  bool small;       // one workgroup per segment
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1239,6 +1380,9 @@ int validate(const dp_decode_shape* sh, Plan* plan) {
   const int64_t useful = (max_units + (int64_t)kWaves * plan->min_chunk - 1) / ((int64_t)kWaves * plan->min_chunk);
   grid = std::max<int64_t>(1, std::max(need, std::min(grid, useful)));
   plan->grid = (int)grid;
+  // (why the line lies here: at paged_decode_small_kernel)
+  plan->small = P == 0 && wpc == 0 && units_per_seq <= kSmallUnits &&
+                (int64_t)sh->batch * sh->n_kv_heads <= cus;
   const int G = sh->n_q_heads / sh->n_kv_heads;
   const size_t waves = (size_t)grid * kWaves;
   // The arrival counters open the workspace, and every call returns the ones
@@ -1328,6 +1472,13 @@ extern "C" int paged_decode_attention(const void* q, const void* k_blocks, const
   a.out_fp32 = shape->out_dtype == DP_OUT_FP32;
   a.min_chunk = plan.min_chunk;
   (void)hipGetLastError();  // clear a stale error left by earlier work
+  if (plan.small) {
+    hipLaunchKernelGGL(fp8 ? paged_decode_small_kernel<true> : paged_decode_small_kernel<false>,
+                       dim3(a.batch * a.hkv), dim3(kSmallWaves * 64), 0, (hipStream_t)stream, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(DP_EIO, "paged_decode: kernel launch failed: %s", hipGetErrorString(e));
+    return DP_OK;
+  }
   if (plan.clear_words)
     hipLaunchKernelGGL(zero_words_kernel, dim3(std::min((plan.clear_words + 255) / 256, 1024)), dim3(256), 0,
                        (hipStream_t)stream, a.arrivals, plan.clear_words);

@@ -337,3 +337,34 @@ def test_largest_batch(gpu_lib, kv):
     assert err <= TOL[kv]
     empty = np.nonzero(w.context_lens == 0)[0]
     assert len(empty) > 0 and np.all(got[empty] == 0.0)
+
+
+@pytest.mark.parametrize("ctx,hq,hkv,kv,c_max", [
+    # the ends of blocks, units and wave turns, an empty sequence among them
+    ([0, 1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 288, 289, 511, 512], 8, 2, "bf16", 512),
+    ([1, 63, 64, 65, 0, 511, 512, 513, 575, 1023, 1024], 16, 1, "fp8_e4m3", 1024),
+    ([300, 7, 129], 7, 7, "bf16", 300),                       # G = 1, c_max not a multiple of a block's tokens
+    ([300, 7, 1000], 35, 5, "fp8_e4m3", 1000),                # G = 7
+    ([1 + 7 * s % 512 for s in range(32)], 64, 8, "bf16", 512),    # as many segments as compute units
+    ([1 + 7 * s % 512 for s in range(33)], 64, 8, "bf16", 512),    # one sequence more: cut segments
+    ([0, 513, 40], 16, 2, "bf16", 513),                       # one unit more: cut segments
+])
+def test_short_contexts(gpu_lib, ctx, hq, hkv, kv, c_max):
+    """Calls of few, short sequences (one workgroup per segment) and the first
+    shapes past them: every row against the oracle, the second call equal to
+    the first, and equal within the bar to the cut segments an explicit
+    minimum slice asks for."""
+    note(f"short contexts: {len(ctx)} sequences {hq}/{hkv} {kv} c_max {c_max}")
+    w = workloads.make_workload(len(ctx), hq, hkv, ctx, c_max=c_max, kv_format=kv, seed=len(ctx) + hq)
+    dev = workloads.to_device(w)
+    got = gpu_out(gpu_lib, w, dev, out_fp32=True)
+    np.testing.assert_array_equal(gpu_out(gpu_lib, w, dev, out_fp32=True), got)
+    ref = oracle_out(w)
+    rows = list(range(len(ctx)))
+    assert np.isfinite(got).all() and max_err(got, ref, rows) <= TOL[kv]
+    assert max_err(gpu_out(gpu_lib, w, dev), ref, rows) <= TOL[kv]
+    cut = gpu_out(gpu_lib, w, dev, out_fp32=True, P=64)
+    assert max_err(cut, ref, rows) <= TOL[kv]
+    for s, t in enumerate(ctx):
+        if t == 0:
+            assert (got[s] == 0).all()
