@@ -596,41 +596,27 @@ __global__ __launch_bounds__(kWaves * 64) void paged_decode_kernel(DecodeArgs a)
   UnitRegs RA;
 
   // ---- 1. prefix of units over sequences ----
-  if (B <= 64 * kWaves) {
-    // Every wave computes all of it, for up to four consecutive sequences a
-    // lane: the four waves write the same values, each reads only what it
-    // wrote itself (a wave's LDS operations complete in order) and no barrier
-    // holds it up (thirteen fp8 sequences of up to 5,395 tokens 20.2 -> 19.8
-    // us, four of up to 487 on eight heads, append included, 12.8 -> 12.2).
+  if (B <= 64) {
+    // Every wave computes all of it, one sequence a lane: the four waves write
+    // the same values, each reads only what it wrote itself (a wave's LDS
+    // operations complete in order) and no barrier holds it up (thirteen fp8
+    // sequences of up to 5,395 tokens 20.2 -> 19.6 us; with two to four
+    // sequences a lane nothing was left of it).
     if constexpr (FP8) {
       for (int i = lane; i < Hkv; i += 64) {
         kscl[i] = a.k_scale[i];
         vscl[i] = a.v_scale[i];
       }
     }
-    const int per = (B + 63) >> 6;
-    int c[kWaves];
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k)
-      c[k] = k < per ? clamp_ctx(a.context_lens[min(lane * per + k, B - 1)], a.max_ctx) : 0;
-    int local = 0;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-      if (k >= per || lane * per + k >= B) c[k] = 0;
-      local += units_of<FP8>(c[k]);
-    }
+    int c = clamp_ctx(a.context_lens[min(lane, B - 1)], a.max_ctx);
+    if (lane >= B) c = 0;
     issue_at(RA, ck, cv);
-    int run = wave_incl_scan(local) - local;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-      const int s = lane * per + k;
-      if (k < per && s < B) {
-        ctxs[s] = c[k];
-        pre[s] = run;
-        run += units_of<FP8>(c[k]);
-        if (s == B - 1) pre[B] = run;
-      }
+    const int incl = wave_incl_scan(units_of<FP8>(c));
+    if (lane < B) {
+      ctxs[lane] = c;
+      pre[lane + 1] = incl;
     }
+    if (lane == 0) pre[0] = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
   } else {

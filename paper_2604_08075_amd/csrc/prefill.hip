@@ -49,7 +49,7 @@
 // same card in turn, before (eight heads by 32 tokens an item; scores, softmax
 // and output products of one tile in sequence) and now: the bf16 chunks 3.26
 // to 3.34 -> 3.18 to 3.21 ms (1,157 to 1,167 TFLOP/s), four fp8 chunks at 2 K
-// to 8 K 1.05 -> 0.95 ms, eleven fresh prompts of 83 to 3,372 tokens 470 ->
+// to 8 K 1.05 -> 0.95 ms, eleven fresh prompts of 179 to 3,372 tokens 470 ->
 // 421 us, 381 tokens at context 20,861 572 -> 297 us, three prompts of up to
 // 493 tokens with GQA 4 18.5 -> 13.2 us.
 //
