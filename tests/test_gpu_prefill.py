@@ -211,6 +211,8 @@ def _edges(qs):
     ([(1001, 1333), (97, 97), (1, 700)], 60, 12, "bf16"),
     # more sequences than a wave has lanes, more rounds of items than are looked up at once
     ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16"),
+    # the largest batch on the split context: 155 KiB of LDS, the most a launch takes
+    ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 3, 1, "bf16"),
 ])
 def test_item_widths(gpu_lib, chunks, hq, hkv, kv):
     """Each width of work item the library chooses between, at the ends of its
