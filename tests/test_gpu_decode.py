@@ -368,3 +368,27 @@ def test_short_contexts(gpu_lib, ctx, hq, hkv, kv, c_max):
     for s, t in enumerate(ctx):
         if t == 0:
             assert (got[s] == 0).all()
+
+
+@pytest.mark.parametrize("ctx,hq,hkv,kv,c_max", [
+    ([0, 1, 31, 32, 33, 256, 257, 288, 289, 500, 511, 512], 8, 2, "bf16", 512),
+    ([1, 64, 65, 512, 513, 575, 1000, 1024], 16, 1, "fp8_e4m3", 1024),
+    ([300, 7, 512], 21, 3, "bf16", 512),
+])
+def test_short_contexts_equal_one_unit_slices(gpu_lib, ctx, hq, hkv, kv, c_max):
+    """The one-workgroup route rounds probabilities as slices of one unit do,
+    each unit on its own maximum, so the two differ by the order of 32-bit sums
+    only.  Both outputs are weighted means of values up to vmax from at most
+    sixteen partials; an exponential, a product and a sum each add a few units
+    of 2^-24: 64 of them in all."""
+    note(f"short contexts against one-unit slices: {len(ctx)} sequences {hq}/{hkv} {kv}")
+    w = workloads.make_workload(len(ctx), hq, hkv, ctx, c_max=c_max, kv_format=kv, seed=77)
+    dev = workloads.to_device(w)
+    one = gpu_out(gpu_lib, w, dev, out_fp32=True)
+    cut = gpu_out(gpu_lib, w, dev, out_fp32=True, P=64 if kv == "fp8_e4m3" else 32)
+    ref = oracle_out(w)
+    vmax = 8.0  # normal values: none of this size
+    err = float(np.abs(one - cut).max())
+    note(f"  max difference {err:.3e}; error {np.linalg.norm(one - ref) / np.linalg.norm(ref):.4e}, "
+         f"slices {np.linalg.norm(cut - ref) / np.linalg.norm(ref):.4e}")
+    assert err <= 64 * 2.0 ** -24 * vmax
