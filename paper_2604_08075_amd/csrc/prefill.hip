@@ -647,9 +647,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
 #pragma unroll
     for (int b = 0; b < NC; ++b) summm(pB, b);
 
-    // this lane holds dims 32 (nn / 2) + 8 lj + 4 (nn % 2) + e of its columns
+    // This lane holds dims 32 (nn / 2) + 8 lj + 4 (nn % 2) + e of its columns.
+    // Idle columns are not stored: the last column's own lane writes its row.
     auto store_row = [&](int b, int n0, auto n_c, float inv, auto at) __attribute__((always_inline)) {
       constexpr int N = decltype(n_c)::value;
+      if (c0 + cg * kWaveCols + 16 * b + li >= ncols) return;
       int tok, row;
       column(b, tok, row);
       const size_t off = (size_t)row * kD + 8 * lj + 16 * n0;
