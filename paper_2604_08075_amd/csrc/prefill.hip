@@ -314,6 +314,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
     const int nb = (T + kBS - 1) / kBS;
     const int32_t* bt = a.block_tables + (size_t)s * a.max_blocks_per_seq;
     const int pmin = T - n + min(c0 + cg * kWaveCols, ncols - 1) / G;  // first position of this wave's columns
+    // Steps this wave computes: up to the sub-tile of its own last position,
+    // not of the item's, and none without a column.  Past them every one of
+    // its probabilities is 0, and 0 times a value that is not finite is not.
+    const int p_end = T - n + (min(c0 + (cg + 1) * kWaveCols, ncols) - 1) / G;
+    const int nt_w = c0 + cg * kWaveCols >= ncols || p_end < kKT * ks ? 0 : (p_end - kKT * ks) / ST + 1;
 
     float cmul = a.scale_log2, vsc = 1.0f;
     if constexpr (FP8) {
@@ -629,23 +634,56 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
       __builtin_amdgcn_sched_barrier(0);
     };
     int j = 0;
-    for (; j + 1 < nt; j += 2) {
+    for (; j + 1 < nt_w; j += 2) {
       step(j, 0, sA, sB, pA, pB, kA, vA);
       step(j + 1, 1, sB, sA, pB, pA, kB, vB);
     }
-    if (j < nt) {
+    if (j < nt_w) {
       step(j, 0, sA, sB, pA, pB, kA, vA);
 #pragma unroll
       for (int b = 0; b < NC; ++b) pB.p[b] = pA.p[b];
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) vf[i] = (nt & 1) ? vfrag(0, i) : vfrag(1, i);
+    for (int i = 0; i < 8; ++i) vf[i] = (nt_w & 1) ? vfrag(0, i) : vfrag(1, i);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int b = 0; b < NC; ++b) pvmm(vf[i], pB, i, b);
 #pragma unroll
     for (int b = 0; b < NC; ++b) summm(pB, b);
+
+    // the item's remaining steps: only this wave's part of the copies, for the
+    // waves that still compute (its last V tile, read above, lies in the slot
+    // that step nt_w leaves alone)
+    auto copy_step = [&](int j, int par, Chunk& kr, Chunk& vr) __attribute__((always_inline)) {
+      Ids t4;
+      bases(idn, t4);
+      clip_v(j, vr);
+#pragma unroll
+      for (int x = 0; x < S * NL; ++x) {
+        store_k(par, x, kr);
+        store_v(par, x, vr);
+      }
+      load(a.k, koff_g, t4, kr);
+      load(a.v, voff_g, tb[0], vr);
+      tb[0] = tb[1];
+      tb[1] = t4;
+      read_ids(j + 5, idn);
+      lds_barrier();
+    };
+    j = nt_w;
+    if (j < nt) {
+      // The loads in flight are waited for here, once: which register set was
+      // loaded last depends on the parity of nt_w, and without this the
+      // compiler would wait for every load in every step below.
+      __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0)
+      if (j & 1) copy_step(j++, 1, kB, vB);
+      for (; j + 1 < nt; j += 2) {
+        copy_step(j, 0, kA, vA);
+        copy_step(j + 1, 1, kB, vB);
+      }
+      if (j < nt) copy_step(j, 0, kA, vA);
+    }
 
     // This lane holds dims 32 (nn / 2) + 8 lj + 4 (nn % 2) + e of its columns.
     // Idle columns are not stored: the last column's own lane writes its row.

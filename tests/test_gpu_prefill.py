@@ -226,3 +226,33 @@ def test_item_widths(gpu_lib, chunks, hq, hkv, kv):
     err = float(np.abs(got[rows] - ref[rows]).max())
     note(f"  max abs err {err:.3e}")
     assert np.isfinite(got).all() and err <= TOL[kv]
+
+
+@pytest.mark.parametrize("n,T,hq,hkv,kv", [
+    (256, 300, 4, 4, "bf16"),         # items of 64 columns
+    (256, 2300, 4, 4, "bf16"),        # of 128, the context split between two waves
+    (256, 2331, 6, 2, "fp8_e4m3"),    # the same, columns that cross tokens
+    (600, 650, 64, 64, "bf16"),       # of 128 to four waves
+    (1000, 1011, 64, 64, "fp8_e4m3"), # of 256
+])
+def test_non_finite_value_reaches_no_further_than_its_tile(gpu_lib, n, T, hq, hkv, kv):
+    """A masked probability is 0, and 0 times a value that is not finite is not
+    0: a column may meet such values up to the end of the 32-token tile that
+    the last of the up to 32 tokens it shares a wave with lies in, and no
+    further, however many tokens its work item has.  Earlier rows keep their
+    bits; the token's own row shows it."""
+    note(f"non-finite value: {n} tokens at {T}, {hq}/{hkv} {kv}")
+    w = workloads.make_prefill([(n, T)], hq, hkv, c_max=T, kv_format=kv, seed=37)
+    dev = workloads.to_device(w)
+    base = gpu_rows(gpu_lib, w, dev)
+    assert np.isfinite(base).all()
+    for t in (T - 1, T - 40):
+        blk, slot = int(w.block_tables[0][t // 16]), t % 16
+        keep = dev["v"][0, blk, :, :, slot].clone()
+        dev["v"][0, blk, :, :, slot] = 0x7F if kv == "fp8_e4m3" else 0x7FC0
+        got = gpu_rows(gpu_lib, w, dev)
+        dev["v"][0, blk, :, :, slot] = keep
+        clean = 32 * (t // 32) - 31 - (T - n)  # rows before it
+        assert clean > 0
+        np.testing.assert_array_equal(got[:clean], base[:clean])
+        assert np.isnan(got[t - (T - n)]).all()
