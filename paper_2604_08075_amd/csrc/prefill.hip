@@ -179,6 +179,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
   __shared__ int ids_lds[kIdCap];
   __shared__ int wsum[kWaves];
   __shared__ int list[kList][2];  // (sequence, tile) of this workgroup's next rounds
+  __shared__ float first_max[kWaves / S][NC][16];  // S > 1: the columns' first reference maxima
   extern __shared__ int tile_pre[];  // [B + 1] items per KV head of sequences 0..s-1, then r0[B], r1[B], T[B]
 
   const int tid = threadIdx.x;
@@ -524,7 +525,24 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
 #pragma unroll
       for (int y = 0; y < 4; ++y) colmax(sA, b, y);
     excess();
+    // Both waves of a pair start from the reference maxima of the first 32
+    // tokens, so that a column's probabilities are rounded as in the variants
+    // without pairs: the variant changes the order of sums only.
+    if (S > 1 && ks == 0) {
+      prepare(0, sA);
+      if (lj == 0)
+#pragma unroll
+        for (int b = 0; b < NC; ++b) first_max[cg][b][li] = mc[b];
+    }
     lds_barrier();  // K tile 0 is read before tile 2 takes its place
+    if (S > 1 && ks > 0) {
+#pragma unroll
+      for (int b = 0; b < NC; ++b) {
+        mc[b] = first_max[cg][b][li];
+        mlim[b] = mc[b] + kSlack;
+      }
+    }
+    if constexpr (S > 1) excess();
 
     Probs pA, pB;
 #pragma unroll

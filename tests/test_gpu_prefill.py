@@ -256,3 +256,35 @@ def test_non_finite_value_reaches_no_further_than_its_tile(gpu_lib, n, T, hq, hk
         assert clean > 0
         np.testing.assert_array_equal(got[:clean], base[:clean])
         assert np.isnan(got[t - (T - n)]).all()
+
+
+@pytest.mark.parametrize("chunks,hq,hkv,kv", [
+    ([(300, 1900), (33, 64), (70, 70), (1, 33)], 8, 2, "bf16"),
+    ([(130, 1501), (40, 40), (5, 2000)], 16, 1, "fp8_e4m3"),
+    ([(300, 1900)], 64, 8, "bf16"),
+])
+def test_split_context_rounds_alike(gpu_lib, chunks, hq, hkv, kv):
+    """With a max_context_len above 2,048 two waves share a column's context.
+    Both start from the maximum of the first 32 tokens, so probabilities are
+    rounded as without the split and the outputs differ by the order of 32-bit
+    sums only: one addition per 32-token tile (at most 63) and some 64 further
+    units of 2^-24 from exponentials, weights and the division, of values below
+    8."""
+    note(f"split context: {chunks} {hq}/{hkv} {kv}")
+    w = workloads.make_prefill(chunks, hq, hkv, c_max=4096, kv_format=kv, seed=41)
+    dev = workloads.to_device(w)
+    total_q = int(w.meta["q_start"][-1])
+    outs = []
+    for longest in (2048, 4096):
+        shape = gpu_lib.prefill_shape(w.batch, hq, hkv, w.max_blocks_per_seq, longest, w.num_blocks, total_q,
+                                      kv_fp8=kv == "fp8_e4m3", out_fp32=True)
+        out = torch.full((total_q, hq, 128), float("nan"), device="cuda")
+        gpu_lib.chunked_prefill_attention(dev["q"], dev["k"][0], dev["v"][0], dev["block_tables"],
+                                          dev["context_lens"], dev["q_start"], w.scale, out, shape, dev["k_scale"],
+                                          dev["v_scale"])
+        torch.cuda.synchronize()
+        outs.append(out.cpu().numpy())
+    assert np.isfinite(outs[0]).all()
+    err = float(np.abs(outs[0] - outs[1]).max())
+    note(f"  max difference {err:.3e}")
+    assert err <= 128 * 2.0 ** -24 * 8.0
