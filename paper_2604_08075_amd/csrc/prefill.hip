@@ -887,27 +887,43 @@ extern "C" int chunked_prefill_attention(const void* q, const void* k_blocks, co
   a.total_q = (int32_t)sh->total_q;
   (void)hipGetLastError();
   hipStream_t st = (hipStream_t)stream;
-  // The variant, by how far the columns fill the compute units.  n(c): items
-  // of c columns.
-  //  - n(256) covers every compute unit: eight waves of 32 columns, whose 256
-  //    columns share each K and V tile they copy.
-  //  - n(128) still does: four-wave workgroups of 128 columns, two to a unit,
-  //    which overlap each other's set-up and epilogue (three ragged prompts,
-  //    190 items of 256 columns, GQA 12: 55 us; 66 with 256-column items, 63
-  //    with the split below).
-  //  - fewer, and contexts may be long: 128 columns to eight waves in pairs,
-  //    each of a pair on half the KV steps (381 tokens at context 20,861: 329
-  //    us; 374 with 128 columns to four waves, 510 with 256 to eight).
-  //  - fewer, and contexts of at most 2,048 tokens: 64 columns to four waves.
-  //    The item is set-up and a few steps, and neither more waves on it nor a
-  //    fold pay (three prompts of up to 493 tokens: 14.9 us; 17.3 with the
-  //    split, 16.6 with 128 columns).
+  // The variant.  items(c): items of c columns, were the chunks all of one
+  // length.  (Times: one call from a replayed graph.)
+  //  - The columns fill every compute unit with items of 256: eight waves of 32
+  //    columns, whose 256 columns share each K and V tile they copy.
+  //  - Contexts may be long (max_context_len > 2048): an item is a chain of KV
+  //    steps, so waves work in pairs, each of a pair on half of them.  64
+  //    columns to eight waves if no more such items than compute units or no
+  //    sequence (on average) with more columns (100 tokens at context 8,000 on
+  //    64/8 heads: 95 us, 120 with 128 columns; 64 chunks of 4 tokens at about
+  //    4,000: 182 and 196); else 128 columns to eight waves, if these items do
+  //    not outnumber the compute units (381 tokens at context 20,861: 297 us;
+  //    400 with 64 columns to four waves without pairs).  Where the contexts
+  //    are short all the same, the pairs' fold costs up to 5 us (nine fresh
+  //    prompts below 400 tokens on 16/4 heads: 18.3 us, 13.1 with 64 columns
+  //    to four waves); the host does not know them.
+  //  - Otherwise two four-wave workgroups to a unit, which overlap each
+  //    other's set-up and epilogue: of 64 columns while these items all run at
+  //    once or no sequence has more columns (ten chunks of 200 tokens at
+  //    context 1,000 on 16/2 heads: 28 us; 32 with 128 columns), else of 128
+  //    (five chunks of 100 tokens at 500 on 64/8 heads, 280 items of 128: 22
+  //    us; 26 with 64 columns, 29 with pairs, which take a second round; 1,000
+  //    one-token chunks at about 200 on 64/8 heads: 182 us with 64 columns,
+  //    246 with 256).
   const int64_t cus = compute_units();
-  const auto n = [&](int c) { return (sh->total_q * group + c - 1) / c * sh->n_kv_heads; };
-  if (n(256) >= cus) launch<8, 2, 1>(a, fp8, cus, st);
-  else if (n(128) > cus) launch<4, 2, 1>(a, fp8, 2 * cus, st);
-  else if (sh->max_context_len > 2048) launch<8, 2, 2>(a, fp8, cus, st);
-  else launch<4, 1, 1>(a, fp8, 2 * cus, st);
+  const int64_t per_seq = (sh->total_q * group + sh->batch - 1) / sh->batch;
+  const auto items = [&](int c) { return (per_seq + c - 1) / c * sh->batch * sh->n_kv_heads; };
+  const bool may_be_long = sh->max_context_len > 2048;
+  if (per_seq > 64 && (sh->total_q * group + 255) / 256 * sh->n_kv_heads >= cus)
+    launch<8, 2, 1>(a, fp8, cus, st);
+  else if (may_be_long && (per_seq <= 64 || items(64) <= cus))
+    launch<8, 1, 2>(a, fp8, cus, st);
+  else if (may_be_long && items(128) <= cus)
+    launch<8, 2, 2>(a, fp8, cus, st);
+  else if (!may_be_long && (per_seq <= 64 || items(64) <= 2 * cus))
+    launch<4, 1, 1>(a, fp8, 2 * cus, st);
+  else
+    launch<4, 2, 1>(a, fp8, 2 * cus, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(DP_EIO, "chunked_prefill_attention: kernel launch failed: %s", hipGetErrorString(e));
   return DP_OK;

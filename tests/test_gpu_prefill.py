@@ -201,9 +201,14 @@ def _edges(qs):
     # items of 64 columns: one-column remainders, contexts at the ends of 32-token tiles
     ([(1, 1), (16, 16), (17, 33), (8, 64), (15, 95), (31, 96), (33, 97)], 8, 2, "bf16"),
     ([(3, 31), (4, 32), (5, 33), (9, 160)], 16, 1, "fp8_e4m3"),
-    # 128 columns, two waves on halves of the context: odd and even tile counts, chunks that end in either half
+    # 64 columns, two waves on halves of the context: odd and even tile counts, chunks that end in either half
     ([(7, 2100), (33, 2049), (40, 40), (1, 33), (2, 64), (3, 65)], 16, 2, "bf16"),
     ([(7, 2100), (33, 2081), (16, 32), (17, 97)], 16, 1, "fp8_e4m3"),
+    # 128 columns, the same
+    ([(7, 2100), (133, 2049), (90, 90), (1, 33), (92, 124), (153, 165)], 64, 8, "bf16"),
+    ([(107, 2100), (33, 2081), (116, 132), (117, 197)], 96, 16, "fp8_e4m3"),
+    # fewer than 64 columns a sequence, more items than run at once
+    ([(1 + s % 8, 20 + s) for s in range(200)], 32, 4, "bf16"),
     # 128 columns, four waves: GQA 4 and 5 (columns that cross tokens)
     ([(700, 700), (333, 500), (301, 301)], 32, 8, "bf16"),
     ([(701, 800), (333, 333), (1, 1)], 40, 8, "fp8_e4m3"),
@@ -230,8 +235,9 @@ def test_item_widths(gpu_lib, chunks, hq, hkv, kv):
 
 @pytest.mark.parametrize("n,T,hq,hkv,kv", [
     (256, 300, 4, 4, "bf16"),         # items of 64 columns
-    (256, 2300, 4, 4, "bf16"),        # of 128, the context split between two waves
-    (256, 2331, 6, 2, "fp8_e4m3"),    # the same, columns that cross tokens
+    (256, 2300, 4, 4, "bf16"),        # the same, the context split between two waves
+    (256, 2300, 66, 66, "bf16"),      # of 128, the context split
+    (256, 2331, 6, 2, "fp8_e4m3"),    # of 64, split, columns that cross tokens
     (600, 650, 64, 64, "bf16"),       # of 128 to four waves
     (1000, 1011, 64, 64, "fp8_e4m3"), # of 256
 ])
