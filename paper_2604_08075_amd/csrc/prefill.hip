@@ -133,6 +133,17 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
+// Largest of non-negative values over the 64 lanes, by the same moves.
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
 __device__ __forceinline__ i32x4 fp8x8_to_bf16(int lo, int hi) {
   bf16x2 a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false);
   bf16x2 b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true);
@@ -254,6 +265,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
       n = min(row1[lane] - row0[lane], ctx[lane]);
       pre = ctx[lane] - n;
     }
+    const int t_max = (wave_max(pre + n) + kKT - 1) / kKT;  // no tile takes more steps
     auto above = [&](int t) __attribute__((always_inline)) {  // this lane's tiles that attend more than 32 t tokens
       const int x = kKT * t - pre;  // the tile's last token reaches index x of the chunk
       return x <= 0 ? cnt : x > n - 1 ? 0 : cnt - x * G / COLS;
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
         s = lo;
         q = idx - tile_pre[lo];
       } else {
-        int lo = 0, hi = (a.max_ctx + kKT - 1) / kKT;  // largest t that more than k tiles exceed
+        int lo = 0, hi = t_max;  // largest t that more than k tiles exceed
         while (lo < hi) {
           const int mid = (lo + hi + 1) >> 1;
           if (__builtin_amdgcn_readlane(wave_incl_scan(above(mid)), 63) > k) lo = mid;
