@@ -341,19 +341,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
     const int n_ids = min(min(2 * S * nt, nb), kIdCap);
     const int id0 = bt[min(tid, n_ids - 1)];  // the first ids' loads go out before the queries'
     // token of the chunk and row (token, head) of this lane's column in block b; idle columns repeat the last one
-    auto column = [&](int b, int& tok, int& row) __attribute__((always_inline)) {
+    auto column = [&](int b, int& tok, size_t& row) __attribute__((always_inline)) {
       const int cc = min(c0 + cg * kWaveCols + 16 * b + li, ncols - 1);
       tok = cc / G;
-      row = (r0 + tok) * a.hq + g * G + (cc - tok * G);
+      row = (size_t)(r0 + tok) * a.hq + (g * G + (cc - tok * G));
     };
     int pcol[NC];  // position of this lane's columns
     i32x4 qf[NC][4];
 #pragma unroll
     for (int b = 0; b < NC; ++b) {
-      int tok, row;
+      int tok;
+      size_t row;
       column(b, tok, row);
       pcol[b] = T - n + tok;
-      const uint16_t* qp = a.q + (size_t)row * kD + 8 * lj;
+      const uint16_t* qp = a.q + row * kD + 8 * lj;
 #pragma unroll
       for (int c = 0; c < 4; ++c) qf[b][c] = *(const i32x4*)(qp + 32 * c);
     }
@@ -720,9 +721,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
     auto store_row = [&](int b, int n0, auto n_c, float inv, auto at) __attribute__((always_inline)) {
       constexpr int N = decltype(n_c)::value;
       if (c0 + cg * kWaveCols + 16 * b + li >= ncols) return;
-      int tok, row;
+      int tok;
+      size_t row;
       column(b, tok, row);
-      const size_t off = (size_t)row * kD + 8 * lj + 16 * n0;
+      const size_t off = row * kD + 8 * lj + 16 * n0;
       if (a.out_fp32) {
 #pragma unroll
         for (int nn = 0; nn < N; ++nn) *(f32x4*)((float*)a.out + off + 32 * (nn >> 1) + 4 * (nn & 1)) = at(nn) * inv;
@@ -872,9 +874,13 @@ extern "C" int chunked_prefill_attention(const void* q, const void* k_blocks, co
     return fail(DP_EINVAL, "chunked_prefill_attention: scale must be finite and > 0");
 
   const int group = sh->n_q_heads / sh->n_kv_heads;
-  // items of the smallest variant, an upper bound of every one's
-  const int64_t most = (sh->total_q * group + 63) / 64 + sh->batch;
-  if (most > INT32_MAX / 4 / sh->n_kv_heads)
+  // The kernel counts items in 32 bits.  The bound is on tiles of 32 query
+  // tokens of eight heads: items of 256 columns are never more than those.
+  // The variants with smaller items are taken for few columns, or for
+  // sequences that average 64 or fewer: hardly more items than (token, head)
+  // rows of q, of which a device's memory holds fewer than 2^31.
+  const int64_t tiles = (sh->total_q + 31) / 32 + sh->batch;
+  if (tiles * sh->n_kv_heads * (((int64_t)group + 7) / 8) > INT32_MAX / 2)
     return fail(DP_EINVAL, "chunked_prefill_attention: too many query tiles");
 
   PrefillArgs a;

@@ -321,6 +321,25 @@ def test_prefill_bad_pointers_and_scale_rejected_on_host(host_lib):
                                        ctypes.byref(empty), None) == 0   # nothing to do, nothing enqueued
 
 
+def test_prefill_item_bound_follows_the_items_of_the_call(host_lib):
+    """Few query rows of many heads stay accepted (the next step, the launch,
+    fails for want of a device: EIO); more items than 32 bits count are refused."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the accepted call would be launched, on pointers that are not real")
+    L = host_lib.lib()
+
+    def call(heads, total_q):
+        s = pshape(host_lib, batch=4096, n_q_heads=heads, n_kv_heads=heads, total_q=total_q)
+        return L.chunked_prefill_attention(16, 16, 16, 16, 16, 16, 1.0, None, None, 16, ctypes.byref(s), None)
+
+    assert call(140000, 1) == -5
+    assert call(262000, 1) == -5
+    assert call(263000, 1) == -22
+    assert call(8, 1 << 29) == -5
+    assert call(200, 1 << 29) == -22
+
+
 # ---------------------------------------------------------------- KV append validation (host only)
 
 @pytest.mark.parametrize("kw,code", [
