@@ -304,8 +304,11 @@ def _stream_ptr(stream):
         # torch's current stream of its current device, without the Stream
         # object that torch.cuda.current_stream() builds (0.2 us, 2.7 with it:
         # more than half of a small call's time on the host)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            if torch.cuda.is_initialized():
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # (torch does not promise these two names)
+            pass
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -280,6 +280,17 @@ def test_decoder_wrapper_constructs_on_host(host_lib):
         host_lib.PagedDecoder(4, 8, 2, 64, 1000, 300, partition_tokens=24, device="cpu")
 
 
+def test_current_stream_without_torchs_private_names(host_lib, monkeypatch):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert host_lib._stream_ptr(None) == 1234
+    assert host_lib._stream_ptr(types.SimpleNamespace(cuda_stream=77)) == 77 and host_lib._stream_ptr(5) == 5
+
+
 # ---------------------------------------------------------------- chunked prefill (host-side validation only)
 
 def pshape(host_lib, **kw):
