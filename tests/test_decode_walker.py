@@ -22,6 +22,11 @@ its host launcher do it, and checks on random batches that
     never reads an unpublished record and leaves every counter at zero, under
     any interleaving of the waves' steps.
 
+Calls of few, short sequences take another kernel, one workgroup per segment
+(takes_one_workgroup, simulate_small): there every table entry read is one of
+the sequence's own live blocks, the waves cover every unit once, and the fold
+reads every value of every record once, from where its owner put it.
+
 A kernel change to any of these must be mirrored here.
 """
 from __future__ import annotations
@@ -32,6 +37,7 @@ import numpy as np
 import pytest
 
 WAVES = 4               # waves per workgroup
+SMALL_WAVES = 8         # waves per workgroup of the one-workgroup-per-segment kernel
 MAX_UNITS_PER_WAVE = 256
 FAN_IN = 16             # workgroup pieces per merge group
 
@@ -48,6 +54,54 @@ def host_plan(ctx, hkv, fp8, max_ctx, partition_tokens=0, wgs_per_cu=0, cus=256,
     return max(1, max(need, min(grid, useful))), min_chunk, unit
 
 
+def takes_one_workgroup(ctx, hkv, fp8, max_ctx, partition_tokens=0, wgs_per_cu=0, cus=256):
+    """Whether the launcher gives every segment one workgroup of SMALL_WAVES waves."""
+    units_per_seq = -(-max_ctx // (64 if fp8 else 32))
+    return partition_tokens == 0 and wgs_per_cu == 0 and units_per_seq <= 2 * SMALL_WAVES and len(ctx) * hkv <= cus
+
+
+def simulate_small(ctx, hkv, fp8, max_ctx, max_blocks_per_seq, group):
+    """The index arithmetic of the kernel of one workgroup per segment, checked
+    as it goes.  Returns the block-table entries read, as (s, block)."""
+    UT = 64 if fp8 else 32
+    UB = UT // 16
+    B = len(ctx)
+    reads = []
+    for wg in range(B * hkv):
+        s, g = wg // hkv, wg % hkv
+        assert 0 <= s < B and 0 <= g < hkv
+        T = min(max(int(ctx[s]), 0), max_ctx)
+        nb, nus = -(-T // 16), -(-T // UT)
+        last = max(nb - 1, 0)
+        computed, written = [], []
+        for w in range(SMALL_WAVES):
+            units = [u for u in (w, w + SMALL_WAVES) if u < nus]
+            for u in units:
+                for b in range(UB):  # the unit's blocks, each read by some lanes
+                    blk = min(u * UB + b, last)
+                    assert 0 <= blk < nb <= max_blocks_per_seq, (s, u, b)
+                    assert blk == u * UB + b or (u * UB + b) * 16 >= T  # a stand-in only past the end, masked
+                    reads.append((s, blk))
+            computed += units
+            if units:
+                written.append(w)
+        assert sorted(computed) == list(range(nus))
+        assert written == list(range(min(nus, SMALL_WAVES)))  # the records the fold reads
+        # fold thread p reads head p / 32, dims 4 (p % 32) .. + 4, from where
+        # the lane of that head (li) and dim (16 nn + 4 lj + e) stored them
+        stored = {(nn * 1024 + (lj * 16 + li) * 16): (li, 16 * nn + 4 * lj)
+                  for nn in range(8) for lj in range(4) for li in range(16)}
+        seen = set()
+        for p in range(group * 32):
+            assert p < SMALL_WAVES * 64
+            hd, d0 = p >> 5, (p & 31) * 4
+            assert stored[(d0 >> 4) * 1024 + (hd + 4 * (d0 & 15)) * 16] == (hd, d0)
+            assert 8192 + hd * 8 + 8 <= 8192 + 512
+            seen.add((hd, d0))
+        assert len(seen) == group * 32
+    return reads
+
+
 class Walk:
     __slots__ = ("s", "g", "j", "nus")
 
@@ -62,7 +116,9 @@ class Walk:
 
 
 def simulate(ctx, hkv, fp8, max_ctx, max_blocks_per_seq, partition_tokens=0, wgs_per_cu=0, cus=256):
-    """Run the kernel's index arithmetic; returns what it touched."""
+    """Run the index arithmetic of the kernel that cuts segments; returns what it touched."""
+    if takes_one_workgroup(ctx, hkv, fp8, max_ctx, partition_tokens, wgs_per_cu, cus):
+        partition_tokens = 64 if fp8 else 32  # such a call cuts segments if it asks for a slice: the same plan
     B = len(ctx)
     grid, min_chunk, UT = host_plan(ctx, hkv, fp8, max_ctx, partition_tokens, wgs_per_cu, cus)
     UB = UT // 16
@@ -258,6 +314,30 @@ def test_empty_and_tiny_batches(ctx):
         for cus in (1, 256):
             sim = simulate(ctx, 2, fp8, max(max(ctx), 1), 8, cus=cus)
             check(sim, 2)
+
+
+@pytest.mark.parametrize("ctx,hkv,group,fp8,max_ctx", [
+    ([0, 1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 288, 289, 511, 512], 2, 4, False, 512),
+    ([1, 63, 64, 65, 0, 511, 512, 513, 575, 1023, 1024], 1, 16, True, 1024),
+    ([300, 7, 129], 7, 1, False, 300),
+    ([300, 7, 1000], 5, 7, True, 1000),
+    ([0], 1, 8, False, 0),
+    ([0, 0, 5], 2, 8, True, 5),
+])
+def test_one_workgroup_per_segment(ctx, hkv, group, fp8, max_ctx):
+    """The ends of blocks, units and wave turns; every live block is read."""
+    assert takes_one_workgroup(ctx, hkv, fp8, max_ctx)
+    reads = simulate_small(ctx, hkv, fp8, max_ctx, max(-(-max_ctx // 16), 1), group)
+    assert set(reads) == {(s, b) for s, t in enumerate(ctx) for b in range(-(-t // 16))}
+
+
+def test_one_workgroup_per_segment_ends_where_the_launcher_says():
+    for fp8, most in ((False, 512), (True, 1024)):
+        assert takes_one_workgroup([1] * 32, 8, fp8, most)
+        assert not takes_one_workgroup([1] * 33, 8, fp8, most)       # more segments than compute units
+        assert not takes_one_workgroup([1] * 32, 8, fp8, most + 1)   # more than two units a wave
+        assert not takes_one_workgroup([1] * 32, 8, fp8, most, partition_tokens=64)
+        assert not takes_one_workgroup([1] * 32, 8, fp8, most, wgs_per_cu=1)
 
 
 def test_benchmark_shapes():
