@@ -113,7 +113,9 @@ def test_random_batches_every_row(gpu_lib):
     heads, 1-130 sequences with empty ones among them, C_max 64-5000, minimum
     slice and workgroups per compute unit), every row against the oracle.  Each
     shape is called twice on one workspace: the second call starts its first
-    unit from the tiles the first call kept, and must equal it bit for bit."""
+    unit from the tiles the first call kept, and must equal it bit for bit.
+    Shapes drawn without a launch shape, some of which take one workgroup per
+    segment, are run with cut segments of at least one unit as well."""
     rng = np.random.default_rng(2604)
     for case in range(60):
         kv = ["bf16", "fp8_e4m3"][int(rng.integers(0, 2))]
@@ -132,13 +134,15 @@ def test_random_batches_every_row(gpu_lib):
         note(f"case {case}: kv={kv} G={G} Hkv={Hkv} B={B} C_max={cmax} P={P} wgs={wgs} seed={seed}")
         w = workloads.make_workload(B, G * Hkv, Hkv, list(ctx), c_max=cmax, kv_format=kv, seed=seed)
         d = workloads.to_device(w)
-        dec = gpu_lib.PagedDecoder(w.batch, w.n_q_heads, w.n_kv_heads, w.max_blocks_per_seq, w.max_context_len,
-                                   w.num_blocks, kv_fp8=kv == "fp8_e4m3", out_fp32=True, partition_tokens=P,
-                                   workgroups_per_cu=wgs)
-        first = gpu_out(gpu_lib, w, d, dec=dec)
-        assert np.array_equal(gpu_out(gpu_lib, w, d, dec=dec), first), "the second call differs from the first"
-        err = max_err(first, oracle_out(w), list(range(B)))
-        assert np.isfinite(first).all() and err <= TOL[kv], f"case {case}: max abs err {err:.3e}"
+        ref = oracle_out(w)
+        for slices in [P] + ([64 if kv == "fp8_e4m3" else 32] if P == 0 and wgs == 0 else []):
+            dec = gpu_lib.PagedDecoder(w.batch, w.n_q_heads, w.n_kv_heads, w.max_blocks_per_seq, w.max_context_len,
+                                       w.num_blocks, kv_fp8=kv == "fp8_e4m3", out_fp32=True,
+                                       partition_tokens=slices, workgroups_per_cu=wgs)
+            first = gpu_out(gpu_lib, w, d, dec=dec)
+            assert np.array_equal(gpu_out(gpu_lib, w, d, dec=dec), first), "the second call differs from the first"
+            err = max_err(first, ref, list(range(B)))
+            assert np.isfinite(first).all() and err <= TOL[kv], f"case {case} P={slices}: max abs err {err:.3e}"
 
 
 def test_partition_invariance(gpu_lib):
@@ -169,10 +173,11 @@ def test_partition_invariance(gpu_lib):
         assert (diff <= bound).all()
 
 
-def test_one_token_context_returns_v_exactly(gpu_lib):
+@pytest.mark.parametrize("P", [0, 32])  # one workgroup per segment; cut segments
+def test_one_token_context_returns_v_exactly(gpu_lib, P):
     note("ctx=1 returns V")
     w = workloads.make_workload(5, 16, 2, [1] * 5, c_max=64, seed=4)
-    got = gpu_out(gpu_lib, w)
+    got = gpu_out(gpu_lib, w, P=P)
     for s in range(5):
         blk = w.block_tables[s, 0]
         for h in range(16):
@@ -180,11 +185,12 @@ def test_one_token_context_returns_v_exactly(gpu_lib):
             assert np.array_equal(got[s, h], v)
 
 
-def test_empty_context_gives_zero_rows(gpu_lib):
+@pytest.mark.parametrize("P", [0, 32])  # one workgroup per segment; cut segments
+def test_empty_context_gives_zero_rows(gpu_lib, P):
     note("ctx=0 rows")
     w = workloads.make_workload(4, 8, 2, [0, 40, 0, 7], c_max=64, seed=5)
     for fp32 in (False, True):
-        got = gpu_out(gpu_lib, w, out_fp32=fp32)
+        got = gpu_out(gpu_lib, w, out_fp32=fp32, P=P)
         assert np.array_equal(got[[0, 2]], np.zeros((2, 8, 128)))
         ref = oracle_out(w, [1, 3])
         assert max_err(got, ref, [1, 3]) <= TOL["bf16"]
@@ -271,30 +277,33 @@ def test_longest_context_and_gqa16_bf16(gpu_lib):
     assert err <= TOL["bf16"]
 
 
-def test_rotated_layers_read_their_own_pool(gpu_lib):
+@pytest.mark.parametrize("P", [0, 32])  # one workgroup per segment; cut segments
+def test_rotated_layers_read_their_own_pool(gpu_lib, P):
     note("layer rotation")
     w = workloads.make_workload(3, 16, 2, [100, 200, 300], c_max=512, seed=10)
     dev = workloads.to_device(w, layers=3)
-    outs = [gpu_out(gpu_lib, w, dev, layer=l) for l in range(3)]
+    outs = [gpu_out(gpu_lib, w, dev, layer=l, P=P) for l in range(3)]
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
 
 
 def test_workspace_reused_across_shapes(gpu_lib):
     """One zero-filled workspace serves calls of different shapes in turn, including
-    grids of very different widths (a few waves; two workgroups per compute unit;
-    a grid wider than eight workgroups per compute unit, whose counters reach past
-    the fixed counter region): every call equals its fresh-workspace result bit for
-    bit, and every call leaves the counter region at zero."""
+    grids of very different widths (fifteen workgroups; two per compute unit; a
+    grid wider than eight per compute unit, whose counters reach past the fixed
+    counter region) and a call that takes one workgroup per segment and leaves the
+    workspace alone: every call equals its fresh-workspace result bit for bit, and
+    every call leaves the counter region at zero."""
     note("workspace reuse")
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     rng = np.random.default_rng(12)
     wide_ctx = rng.integers(0, 40, 4096)
     wide_ctx[[5, 900, 4000]] = [3000, 700, 1500]
     cases = [  # (workload, decoder kwargs)
-        (workloads.make_workload(3, 8, 2, [300, 17, 90], c_max=320, seed=11), {}),
+        (workloads.make_workload(3, 8, 2, [300, 17, 90], c_max=320, seed=11), {"partition_tokens": 32}),
         (workloads.make_workload(5, 32, 4, [3000, 1, 700, 4096, 2500], c_max=4096, seed=12), {"workgroups_per_cu": 2}),
         (workloads.make_workload(3, 64, 4, [9000, 33, 5000], c_max=16384, kv_format="fp8_e4m3", seed=13), {}),
         (workloads.make_workload(4096, 4, 2, wide_ctx, c_max=65536, seed=14), {}),
+        (workloads.make_workload(3, 8, 2, [300, 17, 90], c_max=320, seed=11), {}),
     ]
     devs, decs, refs = [], [], []
     for w, kw in cases:
@@ -311,7 +320,7 @@ def test_workspace_reused_across_shapes(gpu_lib):
     for dec, n in zip(decs, sizes):
         dec.workspace = shared[:n]
     counter_bytes = 2 * 4 * 8 * 4 * cus   # two int32 counters per wave, up to 8 four-wave workgroups per CU
-    for order in ([0, 1, 2, 3], [3, 0, 3, 1, 2, 0, 3], [2, 1, 0]):
+    for order in ([0, 1, 2, 3, 4], [3, 0, 3, 1, 4, 2, 0, 4, 3], [2, 4, 1, 0]):
         for i in order:
             w, _ = cases[i]
             assert np.array_equal(gpu_out(gpu_lib, w, devs[i], dec=decs[i]), refs[i]), f"case {i} in {order}"

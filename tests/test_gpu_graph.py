@@ -37,10 +37,12 @@ def capture(fn):
     return g
 
 
+@pytest.mark.parametrize("ctx", [[1, 77, 300, 1500, 4096, 0], [1, 77, 300, 512, 33, 0]],
+                         ids=["cut segments", "one workgroup per segment"])
 @pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
-def test_decode_replays_match_eager(gpu_lib, kv):
-    note(f"decode graph, {kv}")
-    w = workloads.make_workload(6, 32, 4, [1, 77, 300, 1500, 4096, 0], c_max=4096, kv_format=kv, seed=51)
+def test_decode_replays_match_eager(gpu_lib, kv, ctx):
+    note(f"decode graph, {kv}, contexts up to {max(ctx)}")
+    w = workloads.make_workload(6, 32, 4, ctx, c_max=max(ctx), kv_format=kv, seed=51)
     d = workloads.to_device(w)
     dec = gpu_lib.PagedDecoder(w.batch, w.n_q_heads, w.n_kv_heads, w.max_blocks_per_seq, w.max_context_len,
                                w.num_blocks, kv_fp8=kv == "fp8_e4m3")

@@ -23,11 +23,11 @@ def note(msg):
     sys.stdout.flush()
 
 
-def both(lib, w, dev, out_fp32=False):
+def both(lib, w, dev, out_fp32=False, P=0):
     """(noalloc output, workspace output) as numpy float32."""
     fp8 = w.kv_format == "fp8_e4m3"
     dec = lib.PagedDecoder(w.batch, w.n_q_heads, w.n_kv_heads, w.max_blocks_per_seq, w.max_context_len,
-                           w.num_blocks, kv_fp8=fp8, out_fp32=out_fp32)
+                           w.num_blocks, kv_fp8=fp8, out_fp32=out_fp32, partition_tokens=P)
     args = (dev["q"], dev["k"][0], dev["v"][0], dev["block_tables"], dev["context_lens"], w.scale)
     ref = dec.new_out()
     dec(*args, ref, dev["k_scale"], dev["v_scale"])
@@ -39,16 +39,17 @@ def both(lib, w, dev, out_fp32=False):
 
 def test_noalloc_equals_workspace_entry_point(gpu_lib):
     cases = [
-        ("short pool (config 2)", workloads.make_config(2), False),
-        ("tiny (config 1), smaller", workloads.make_config(1), False),
+        ("short pool (config 2)", workloads.make_config(2), False, 0),
+        ("tiny (config 1), smaller", workloads.make_config(1), False, 32),
+        ("tiny, one workgroup per segment", workloads.make_config(1), False, 0),
         ("split segments, fp8 GQA 16", workloads.make_workload(3, 64, 4, [9000, 33, 5000], c_max=16384,
-                                                               kv_format="fp8_e4m3", seed=13), True),
-        ("short pool again", workloads.make_config(2), False),
+                                                               kv_format="fp8_e4m3", seed=13), True, 0),
+        ("short pool again", workloads.make_config(2), False, 0),
     ]
-    for name, w, fp32 in cases:
+    for name, w, fp32, P in cases:
         note(f"noalloc: {name}: B={w.batch} {w.n_q_heads}q/{w.n_kv_heads}kv {w.kv_format}")
         dev = workloads.to_device(w)
-        got, ref = both(gpu_lib, w, dev, out_fp32=fp32)
+        got, ref = both(gpu_lib, w, dev, out_fp32=fp32, P=P)
         assert np.isfinite(got).all()
         assert np.array_equal(got, ref), name
         del dev
