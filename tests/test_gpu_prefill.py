@@ -53,7 +53,7 @@ SMALL = [
     ([(1, 40), (1, 129), (1, 1), (1, 500)], 16, 2, "bf16"),          # one-token chunks: decode
     ([(130, 130), (77, 205), (5, 37)], 4, 4, "bf16"),                # G = 1
     ([(96, 300), (31, 31), (200, 700)], 32, 2, "fp8_e4m3"),          # G = 16
-    ([(64, 96), (40, 40)], 12, 2, "bf16"),                           # G = 6: one quad partly idle
+    ([(64, 96), (40, 40)], 12, 2, "bf16"),                           # G = 6: columns that cross tokens
 ]
 
 
@@ -125,7 +125,7 @@ def test_future_tokens_never_reach_earlier_rows(gpu_lib):
 
 def test_random_chunks_every_row(gpu_lib):
     """Forty seeded random prefill shapes (cache format, GQA group 1-16 including
-    groups that leave a head quad partly idle, 1-4 KV heads, 1-5 chunks of
+    groups whose items end inside a token's heads, 1-4 KV heads, 1-5 chunks of
     1-1,500 context tokens each, fresh prompts and chunks over a cached
     prefix, both query tiles, bf16 and fp32 output), every row against the
     oracle; a second call must equal the first bit for bit."""
@@ -171,17 +171,68 @@ def test_longest_context(gpu_lib):
     assert np.isfinite(got).all() and err <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("chunks,hq,hkv", [
-    ([(2048, 2048), (2200, 4096)], 8, 2),     # 266 items: a partial second (backward) round
-    ([(3000, 3000), (1500, 2000)], 8, 4),     # 564 items: a partial third (forward) round
-])
-def test_item_rounds_with_a_partial_last_round(gpu_lib, chunks, hq, hkv):
-    """More (query tile, head group) items than workgroups, not a multiple of them:
-    every row is written (the output starts as NaN) and sampled rows match the oracle."""
-    note(f"prefill rounds {chunks} {hq}/{hkv}")
-    w = workloads.make_prefill(chunks, hq, hkv, c_max=4096, seed=29)
-    total_q = int(w.meta["q_start"][-1])
-    rows = sorted(set(range(0, total_q, 97)) | {total_q - 1, int(w.meta["q_start"][1]) - 1, int(w.meta["q_start"][1])})
+def plan(chunks, hq, hkv, c_max, cus):
+    """The library's variant (waves, column blocks of a wave, waves that share a
+    column's context) for a call, its items, its workgroups and its rounds, by
+    the same arithmetic: a change of the rule shows in the tests that name what
+    they reach."""
+    def up(a, b):
+        return -(-a // b)
+    G, total, batch = hq // hkv, sum(n for n, _ in chunks), len(chunks)
+    per_seq = up(total * G, batch)
+
+    def items(c):
+        return up(per_seq, c) * batch * hkv
+    if per_seq > 64 and up(total * G, 256) * hkv >= cus:
+        v, most = (8, 2, 1), cus
+    elif c_max > 2048 and (per_seq <= 64 or items(64) <= cus):
+        v, most = (8, 1, 2), cus
+    elif c_max > 2048 and items(128) <= cus:
+        v, most = (8, 2, 2), cus
+    elif c_max <= 2048 and (per_seq <= 64 or items(64) <= 2 * cus):
+        v, most = (4, 1, 1), 2 * cus
+    else:
+        v, most = (4, 2, 1), 2 * cus
+    cols = 16 * v[0] * v[1] // v[2]
+    count = sum(up(n * G, cols) for n, _ in chunks) * hkv
+    grid = min((up(total * G, cols) + batch) * hkv, most)
+    return v, count, grid, up(count, grid)
+
+
+ROUNDS = [
+    # (chunks, Hq, Hkv, C_max, variant, items, rounds): one round of every item, then partial second
+    # (backward) and third (forward) rounds, on every variant
+    ([(2048, 2048), (2200, 4096)], 8, 2, 4096, (4, 2, 1), 266, 1),
+    ([(3000, 3000), (1500, 2000)], 8, 4, 4096, (4, 2, 1), 284, 1),
+    ([(1400, 1400), (1500, 2000)], 32, 4, 4096, (8, 2, 1), 364, 2),
+    ([(2048, 2048), (2200, 4096)], 32, 4, 4096, (8, 2, 1), 532, 3),
+    ([(10, 20 + s) for s in range(200)], 32, 4, 512, (4, 2, 1), 800, 2),
+    ([(1 + s % 2 * 132, 133 + s) for s in range(60)], 15, 15, 512, (4, 2, 1), 1350, 3),
+    ([(1 + s % 8, 20 + s) for s in range(200)], 32, 4, 512, (4, 1, 1), 800, 2),
+    ([(1 + s % 8, 20 + s) for s in range(60)], 20, 20, 512, (4, 1, 1), 1200, 3),
+    ([(1 + s % 8, 20 + s) for s in range(100)], 32, 4, 4096, (8, 1, 2), 400, 2),
+    ([(1 + s % 8, 20 + s) for s in range(60)], 20, 10, 4096, (8, 1, 2), 600, 3),
+    ([(1, 20 + s) for s in range(12)] + [(31, 400 + s) for s in range(12)], 64, 8, 4096, (8, 2, 2), 288, 2),
+    # more rounds than are looked up at once, up to 64 sequences and more
+    ([(1, 1 + s % 40) for s in range(64)], 261, 261, 4096, (8, 1, 2), 16704, 66),
+    ([(1, 1 + s % 16) for s in range(2000)], 17, 17, 512, (4, 1, 1), 34000, 67),
+]
+
+
+@pytest.mark.parametrize("case", range(len(ROUNDS)))
+def test_item_rounds_with_a_partial_last_round(gpu_lib, case):
+    """More items than workgroups, not a multiple of them: every row is written
+    (the output starts as NaN) and sampled rows match the oracle."""
+    chunks, hq, hkv, c_max, variant, items, rounds = ROUNDS[case]
+    note(f"prefill rounds case {case}: {len(chunks)} chunks {hq}/{hkv} C_max {c_max}")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus == 256:
+        v, count, grid, r = plan(chunks, hq, hkv, c_max, cus)
+        assert (v, count, r) == (variant, items, rounds) and (rounds == 1 or count % grid != 0)
+    w = workloads.make_prefill(chunks, hq, hkv, c_max=c_max, seed=29)
+    qs = w.meta["q_start"]
+    total_q = int(qs[-1])
+    rows = sorted(set(range(0, total_q, max(97, total_q // 20))) | {total_q - 1, int(qs[1]) - 1, int(qs[1])})
     got = gpu_rows(gpu_lib, w)
     ref = oracle_rows(w, rows)
     err = float(np.abs(got[rows] - ref[rows]).max())
@@ -197,33 +248,33 @@ def _edges(qs):
     return sorted(rows)
 
 
-@pytest.mark.parametrize("chunks,hq,hkv,kv", [
+@pytest.mark.parametrize("chunks,hq,hkv,kv,variant", [
     # items of 64 columns: one-column remainders, contexts at the ends of 32-token tiles
-    ([(1, 1), (16, 16), (17, 33), (8, 64), (15, 95), (31, 96), (33, 97)], 8, 2, "bf16"),
-    ([(3, 31), (4, 32), (5, 33), (9, 160)], 16, 1, "fp8_e4m3"),
+    ([(1, 1), (16, 16), (17, 33), (8, 64), (15, 95), (31, 96), (33, 97)], 8, 2, "bf16", (4, 1, 1)),
+    ([(3, 31), (4, 32), (5, 33), (9, 160)], 16, 1, "fp8_e4m3", (4, 1, 1)),
     # 64 columns, two waves on halves of the context: odd and even tile counts, chunks that end in either half
-    ([(7, 2100), (33, 2049), (40, 40), (1, 33), (2, 64), (3, 65)], 16, 2, "bf16"),
-    ([(7, 2100), (33, 2081), (16, 32), (17, 97)], 16, 1, "fp8_e4m3"),
+    ([(7, 2100), (33, 2049), (40, 40), (1, 33), (2, 64), (3, 65)], 16, 2, "bf16", (8, 1, 2)),
+    ([(7, 2100), (33, 2081), (16, 32), (17, 97)], 16, 1, "fp8_e4m3", (8, 1, 2)),
     # 128 columns, the same
-    ([(7, 2100), (133, 2049), (90, 90), (1, 33), (92, 124), (153, 165)], 64, 8, "bf16"),
-    ([(107, 2100), (33, 2081), (116, 132), (117, 197)], 96, 16, "fp8_e4m3"),
-    # fewer than 64 columns a sequence, more items than run at once
-    ([(1 + s % 8, 20 + s) for s in range(200)], 32, 4, "bf16"),
+    ([(7, 2100), (133, 2049), (90, 90), (1, 33), (92, 124), (153, 165)], 64, 8, "bf16", (8, 2, 2)),
+    ([(27, 2100), (33, 2081), (66, 82), (57, 97), (40, 64)], 96, 16, "fp8_e4m3", (8, 2, 2)),
     # 128 columns, four waves: GQA 4 and 5 (columns that cross tokens)
-    ([(700, 700), (333, 500), (301, 301)], 32, 8, "bf16"),
-    ([(701, 800), (333, 333), (1, 1)], 40, 8, "fp8_e4m3"),
+    ([(700, 700), (333, 500), (301, 301)], 32, 8, "bf16", (4, 2, 1)),
+    ([(701, 800), (333, 333), (1, 1)], 40, 8, "fp8_e4m3", (4, 2, 1)),
     # 256 columns: GQA 5, a remainder of one token
-    ([(1001, 1333), (97, 97), (1, 700)], 60, 12, "bf16"),
-    # more sequences than a wave has lanes, more rounds of items than are looked up at once
-    ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16"),
-    # the largest batch on the split context: 155 KiB of LDS, the most a launch takes
-    ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 3, 1, "bf16"),
+    ([(1001, 1333), (97, 97), (1, 700)], 60, 12, "bf16", (8, 2, 1)),
+    # the largest batch, and on the split context: 155 KiB of LDS, the most a launch takes
+    ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16", (4, 1, 1)),
+    ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 3, 1, "bf16", (8, 1, 2)),
 ])
-def test_item_widths(gpu_lib, chunks, hq, hkv, kv):
+def test_item_widths(gpu_lib, chunks, hq, hkv, kv, variant):
     """Each width of work item the library chooses between, at the ends of its
     tiles and columns; every row is written, edge rows match the oracle."""
     note(f"prefill widths {len(chunks)} chunks {hq}/{hkv} {kv}")
-    w = workloads.make_prefill(chunks, hq, hkv, c_max=max(t for _, t in chunks), kv_format=kv, seed=31)
+    c_max = max(t for _, t in chunks)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or plan(chunks, hq, hkv, c_max, cus)[0] == variant
+    w = workloads.make_prefill(chunks, hq, hkv, c_max=c_max, kv_format=kv, seed=31)
     rows = _edges(w.meta["q_start"])
     rows = rows[:: max(1, len(rows) // 60)]
     got = gpu_rows(gpu_lib, w)
