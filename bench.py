@@ -386,8 +386,7 @@ def measure_prefill(name, steps, warmup, query_tile=0):
                         f"head_dim 128, {w.kv_format} KV, block 16",
             "us_per_launch": ms * 1e3, "flops": flops, "tflops": tfs,
             "roofline": {"bound": "mfma", "achieved": tfs, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                         "frac": tfs / PEAK_BF16_TFLOPS, "kernel": "prefill_kernel"},
-            "query_tile": 32}
+                         "frac": tfs / PEAK_BF16_TFLOPS, "kernel": "prefill_kernel"}}
 
 
 def router_rate(binding, n=1 << 20, intervals=20000):

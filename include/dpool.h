@@ -285,7 +285,9 @@ typedef struct {
 size_t paged_decode_workspace_size(const dp_decode_shape* shape);
 
 /* The minimum tokens per wave slice the library uses for this shape
- * (0 for invalid shapes). */
+ * (0 for invalid shapes).  For a shape that paged_decode_attention gives one
+ * workgroup per pair (below) it is the slice that cut pairs would have;
+ * passed back as partition_tokens it asks for them. */
 int32_t paged_decode_partition_tokens(const dp_decode_shape* shape);
 
 /* Enqueue the decode attention on `stream` (a hipStream_t; NULL = default
@@ -300,6 +302,13 @@ int32_t paged_decode_partition_tokens(const dp_decode_shape* shape);
  * out = sum_p w_p o_p / sum_p w_p: first inside each workgroup (through its
  * LDS), then, for pairs whose slices span several workgroups, the
  * workgroups' partials through the workspace, by the last to finish.
+ * Calls of few, short sequences are not cut: each pair is one workgroup's,
+ * and the workspace is neither read nor written (its size and alignment are
+ * checked all the same).  That holds for partition_tokens and
+ * workgroups_per_cu 0, max_context_len <= 512 (bf16) or 1,024 (e4m3) and at
+ * most one pair per compute unit; either field other than 0 asks for slices.
+ * Both ways round probabilities to bf16 against the maximum of their slice;
+ * outputs differ by no more than that rounding.
  * The workspace also keeps, for each wave, the cache tiles its first unit
  * read; the next call starts loading those tiles before it has found its
  * own, and loads again where they differ.  A call with the context lengths
@@ -388,6 +397,8 @@ int kv_cache_append(const void* k_new, const void* v_new, void* k_blocks, void* 
 /* Values that break it (or q_start out of order) are clamped: no access    */
 /* leaves the buffers, rows past min(n, T) are left unwritten and rows of   */
 /* overlapping ranges are unspecified.  No workspace; nothing is allocated. */
+/* A cached V value that is not finite shows in its token's row and later    */
+/* ones, and may show in rows up to 62 positions earlier, in none before.    */
 /* Supported: head_dim 128, block_size 16, Hq a multiple of Hkv,            */
 /* batch <= 4096, max_context_len <= 65536 (the long pool's C_max).          */
 /* ------------------------------------------------------------------------ */

@@ -1117,16 +1117,19 @@ template __global__ void paged_decode_kernel<true>(DecodeArgs);
 //
 // What bounds a call of a few short sequences is the chain of dependent loads
 // and exchanges, not bytes.  Here the chain is short: the sequence is known
-// from the workgroup's index, so its context length and queries are
-// loaded at once, then block ids, then K and V, and the waves' sums meet in
-// LDS.  Each of the
-// eight waves has at most two of the segment's units, so all of its loads are
-// in flight together.  A whole segment comes through one compute unit, which
-// takes about 3 us for sixteen units: beyond that, or with more segments than
-// compute units, cut segments are quicker (one layer, us, cut / here: 4
-// sequences of up to 512 tokens on 8/2 heads 10.9 / 9.4; 3 on 64/8 11.7 /
-// 10.4; 32 on 64/8, 256 segments, 15.1 / 14.6, but 64, 512 segments, 20.0 /
-// 24.9; 8 of up to 1,024 tokens, 32 units, 13.3 / 19.2).
+// from the workgroup's index, so its context length and queries are loaded at
+// once, then block ids, then K and V, and the waves' sums meet in LDS.  Each
+// of the eight waves has at most two of the segment's units, so all of its
+// loads are in flight together; longer segments are cut.  So are more
+// segments than compute units, where this kernel needs a second round.
+// Measured, one layer in a replayed graph, us, cut (its first units' tiles
+// known from the call before) / here: 4 sequences of up to 512 tokens on 8/2
+// heads 9.8 / 8.3; on 64/8 heads, sequences of 512 tokens: one 10.1 / 9.3,
+// sixteen 12.0 / 12.0, 32 (256 segments) 14.6 / 13.2; 32 of up to 512 tokens
+// 12.4 / 11.9, of up to 51 7.7 / 4.4.  The cut is quicker where its slices
+// happen to end with the workgroups, as for 32 sequences of exactly 256 tokens,
+// 9.9 / 11.2, which the host cannot see.  Above, with 320 segments: 19.8 / 22.4
+// at 512 tokens, 14.9 / 20.2 at up to 512, 7.8 / 6.3 at up to 51.
 constexpr int kSmallWaves = 8;
 constexpr int kSmallUnits = 2 * kSmallWaves;
 
@@ -1194,8 +1197,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void paged_decode_small_kernel(De
     if (two) {
       // The second unit on a maximum of its own, as in slices of one unit: a
       // probability at its unit's maximum is 1 and not rounded (a running
-      // maximum over both units: error against 64 bits 1.15e-3 of the norm,
-      // 1.13e-3 this way, over four layers of up to 512 tokens).
+      // maximum over both units: error against 64 bits 1.20e-3 of the norm,
+      // 1.18e-3 this way, over four layers of up to 512 tokens).
       float m1 = -INFINITY, l1 = 0.f;
       f32x4 acc1[8];
 #pragma unroll

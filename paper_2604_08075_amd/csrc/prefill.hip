@@ -19,7 +19,8 @@
 //
 // A workgroup's waves share the K and V of 32 tokens (a sub-tile, two blocks)
 // through LDS; each wave owns 16 NC columns and keeps their queries and
-// outputs in registers.  Per step:
+// outputs in registers.  A wave computes up to the tile of its own last token
+// and only takes part in the copies of the item's later steps.  Per step:
 //   * S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (rows: KV tokens, columns:
 //     16 (token, head) pairs), the K rows read from LDS in a token order
 //     chosen so that each lane's eight scores are the eight tokens its
@@ -38,20 +39,20 @@
 // left to itself the compiler sinks the softmax to its use, one step later,
 // and matrix and vector work take turns.
 //
-// What bounds it: power.  The card lowers its clock under this load (2.2 GHz
+// What bounds it: power.  The card lowers its clock under this load (2.1 GHz
 // of 2.4 on the four 2,048-token bf16 chunks at contexts of 2 K to 32 K), so
 // energy per product counts as much as cycles.  On normal data a loop of
-// nothing but 16x16x32 products reaches 2,044 TFLOP/s, one of 32x32x16
-// products 1,808 (2,414 and 2,486 on zeros), so the 32x32 shape, which needs
+// nothing but 16x16x32 products reaches 1,996 TFLOP/s, one of 32x32x16
+// products 1,825 (2,443 and 2,458 on zeros), so the 32x32 shape, which needs
 // half the operand reads, still lost here: 1,120 TFLOP/s at 2.0 GHz.  Waves of
 // 64 columns (four of them, half the LDS reads per product) came to 1,114 to
 // 1,198: one wave on a SIMD has nothing to fill its own stalls with.  Measured,
 // same card in turn, before (eight heads by 32 tokens an item; scores, softmax
 // and output products of one tile in sequence) and now: the bf16 chunks 3.26
-// to 3.34 -> 3.18 to 3.21 ms (1,157 to 1,167 TFLOP/s), four fp8 chunks at 2 K
-// to 8 K 1.05 -> 0.95 ms, eleven fresh prompts of 179 to 3,372 tokens 470 ->
-// 421 us, 381 tokens at context 20,861 572 -> 297 us, three prompts of up to
-// 493 tokens with GQA 4 18.5 -> 13.2 us.
+// -> 3.13 ms (1,184 TFLOP/s), four fp8 chunks at 2 K to 8 K 1.05 -> 0.95 ms,
+// eleven fresh prompts of 179 to 3,372 tokens 471 -> 424 us, 381 tokens at
+// context 20,861 571 -> 298 us, three prompts of up to 493 tokens with GQA 4
+// 18.5 -> 13.3 us.
 //
 // LDS tiles: K rows are 320 bytes apart with 32 more in every second group of
 // eight, V rows 64 with 32 after every eight, so that the sixteen lanes one
@@ -251,9 +252,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a) 
   // backwards (r odd), so every workgroup's items sum to about the same work.
   // A workgroup's tiles of up to kList rounds are found at once, each by one
   // wave.  Up to 64 sequences (one a lane): the tile of rank k by a search for
-  // the step count that just over k tiles exceed.  With more, whose sums even
-  // out by themselves, the tiles are numbered from the end of the batch
-  // backwards.
+  // the step count that just over k tiles exceed.  With more, the tiles are
+  // numbered from the end of the batch backwards, and the sums even out with
+  // their number only (replayed on the CPU for fresh prompts of median 600
+  // tokens on 32/4 heads, the busiest workgroup is 19% above the mean at 65
+  // sequences, 13% at 100, 6% at 400; 1% were they ranked).
   const int nwg = gridDim.x, wg = blockIdx.x;
   auto item_of = [&](int round) __attribute__((always_inline)) {
     return round * nwg + ((round & 1) ? nwg - 1 - wg : wg);
