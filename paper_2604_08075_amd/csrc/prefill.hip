@@ -878,10 +878,9 @@ extern "C" int chunked_prefill_attention(const void* q, const void* k_blocks, co
 
   const int group = sh->n_q_heads / sh->n_kv_heads;
   // The kernel counts items in 32 bits.  The bound is on tiles of 32 query
-  // tokens of eight heads: items of 256 columns are never more than those.
-  // The variants with smaller items are taken for few columns, or for
-  // sequences that average 64 or fewer: hardly more items than (token, head)
-  // rows of q, of which a device's memory holds fewer than 2^31.
+  // tokens of eight heads: items of 256 columns are never more than those, and
+  // the variants with smaller items are taken only where the columns make
+  // fewer items of 256 than there are compute units.
   const int64_t tiles = (sh->total_q + 31) / 32 + sh->batch;
   if (tiles * sh->n_kv_heads * (((int64_t)group + 7) / 8) > INT32_MAX / 2)
     return fail(DP_EINVAL, "chunked_prefill_attention: too many query tiles");
@@ -908,38 +907,47 @@ extern "C" int chunked_prefill_attention(const void* q, const void* k_blocks, co
   a.total_q = (int32_t)sh->total_q;
   (void)hipGetLastError();
   hipStream_t st = (hipStream_t)stream;
-  // The variant.  items(c): items of c columns, were the chunks all of one
-  // length.  (Times: one call from a replayed graph.)
-  //  - The columns fill every compute unit with items of 256: eight waves of 32
-  //    columns, whose 256 columns share each K and V tile they copy.
+  // The variant.  full(c): items of c columns, were the chunks one list;
+  // items(c): the same, were they all of one length.  (Times: one call from a
+  // replayed graph.)
+  //  - full(256) covers every compute unit: eight waves of 32 columns, whose 256
+  //    columns share each K and V tile they copy.  That holds for sequences of
+  //    few columns too, as some may be long: 2,048 tokens at 8,192 beside 500
+  //    decodes at about 2,000 on 64/8 heads 1,115 us, 1,413 with 64-column
+  //    items (1,000 decodes alone, at about 200: 247 and 181).
+  //  - full(128) still does: four-wave workgroups of 128 columns, two to a unit,
+  //    which overlap each other's set-up and epilogue.
   //  - Contexts may be long (max_context_len > 2048): an item is a chain of KV
   //    steps, so waves work in pairs, each of a pair on half of them.  64
-  //    columns to eight waves if no more such items than compute units or no
-  //    sequence (on average) with more columns (100 tokens at context 8,000 on
-  //    64/8 heads: 95 us, 120 with 128 columns; 64 chunks of 4 tokens at about
-  //    4,000: 182 and 196); else 128 columns to eight waves, if these items do
-  //    not outnumber the compute units (381 tokens at context 20,861: 297 us;
-  //    400 with 64 columns to four waves without pairs).  Where the contexts
-  //    are short all the same, the pairs' fold costs up to 5 us (nine fresh
-  //    prompts below 400 tokens on 16/4 heads: 18.3 us, 13.1 with 64 columns
-  //    to four waves); the host does not know them.
-  //  - Otherwise two four-wave workgroups to a unit, which overlap each
-  //    other's set-up and epilogue: of 64 columns while these items all run at
-  //    once or no sequence has more columns (ten chunks of 200 tokens at
-  //    context 1,000 on 16/2 heads: 28 us; 32 with 128 columns), else of 128
-  //    (five chunks of 100 tokens at 500 on 64/8 heads, 280 items of 128: 22
-  //    us; 26 with 64 columns, 29 with pairs, which take a second round; 1,000
-  //    one-token chunks at about 200 on 64/8 heads: 182 us with 64 columns,
-  //    246 with 256).
+  //    columns to eight waves if these items do not outnumber the compute
+  //    units, or no sequence (on average) has more columns (100 tokens at
+  //    context 8,000 on 64/8 heads: 95 us, 120 with 128 columns); else 128
+  //    columns to eight waves while those items fit one round (381 tokens at
+  //    context 20,861: 297 us; 400 with 64 columns to four waves without
+  //    pairs), or where a few long chunks among sequences of few columns hide
+  //    in the average (381 tokens at 20,861 beside 63 decodes at 1,000: 356 us,
+  //    504 with 64).  Where the contexts are short all the same, the pairs' fold
+  //    costs up to 5 us (nine fresh prompts below 400 tokens on 16/4 heads: 18.3
+  //    us, 13.1 with 64 columns to four waves); the host does not know them.
+  //  - Otherwise two four-wave workgroups to a unit again: of 64 columns where
+  //    contexts are at most 2,048 and these items all run at once, or sequences
+  //    have no more columns (ten chunks of 200 tokens at context 1,000 on 16/2
+  //    heads: 28 us; 32 with 128 columns), else of 128 (five chunks of 100
+  //    tokens at 500 on 64/8 heads, 280 items of 128: 22 us; 26 with 64 columns,
+  //    29 with pairs, which take a second round; but 381 tokens at 20,861 beside
+  //    20 decodes at 1,000, 352 items of 128: 373 us, 334 with pairs).
   const int64_t cus = compute_units();
   const int64_t per_seq = (sh->total_q * group + sh->batch - 1) / sh->batch;
+  const auto full = [&](int c) { return (sh->total_q * group + c - 1) / c * sh->n_kv_heads; };
   const auto items = [&](int c) { return (per_seq + c - 1) / c * sh->batch * sh->n_kv_heads; };
   const bool may_be_long = sh->max_context_len > 2048;
-  if (per_seq > 64 && (sh->total_q * group + 255) / 256 * sh->n_kv_heads >= cus)
+  if (full(256) >= cus)
     launch<8, 2, 1>(a, fp8, cus, st);
-  else if (may_be_long && (per_seq <= 64 || items(64) <= cus))
+  else if (full(128) > cus)
+    launch<4, 2, 1>(a, fp8, 2 * cus, st);
+  else if (may_be_long && full(64) <= cus && (per_seq <= 64 || items(64) <= cus))
     launch<8, 1, 2>(a, fp8, cus, st);
-  else if (may_be_long && items(128) <= cus)
+  else if (may_be_long && (per_seq <= 64 || items(128) <= cus))
     launch<8, 2, 2>(a, fp8, cus, st);
   else if (!may_be_long && (per_seq <= 64 || items(64) <= 2 * cus))
     launch<4, 1, 1>(a, fp8, 2 * cus, st);

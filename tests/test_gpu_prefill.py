@@ -181,13 +181,18 @@ def plan(chunks, hq, hkv, c_max, cus):
     G, total, batch = hq // hkv, sum(n for n, _ in chunks), len(chunks)
     per_seq = up(total * G, batch)
 
+    def full(c):
+        return up(total * G, c) * hkv
+
     def items(c):
         return up(per_seq, c) * batch * hkv
-    if per_seq > 64 and up(total * G, 256) * hkv >= cus:
+    if full(256) >= cus:
         v, most = (8, 2, 1), cus
-    elif c_max > 2048 and (per_seq <= 64 or items(64) <= cus):
+    elif full(128) > cus:
+        v, most = (4, 2, 1), 2 * cus
+    elif c_max > 2048 and full(64) <= cus and (per_seq <= 64 or items(64) <= cus):
         v, most = (8, 1, 2), cus
-    elif c_max > 2048 and items(128) <= cus:
+    elif c_max > 2048 and (per_seq <= 64 or items(128) <= cus):
         v, most = (8, 2, 2), cus
     elif c_max <= 2048 and (per_seq <= 64 or items(64) <= 2 * cus):
         v, most = (4, 1, 1), 2 * cus
@@ -214,8 +219,8 @@ ROUNDS = [
     ([(1 + s % 8, 20 + s) for s in range(60)], 20, 10, 4096, (8, 1, 2), 600, 3),
     ([(1, 20 + s) for s in range(12)] + [(31, 400 + s) for s in range(12)], 64, 8, 4096, (8, 2, 2), 288, 2),
     # more rounds than are looked up at once, up to 64 sequences and more
-    ([(1, 1 + s % 40) for s in range(64)], 261, 261, 4096, (8, 1, 2), 16704, 66),
-    ([(1, 1 + s % 16) for s in range(2000)], 17, 17, 512, (4, 1, 1), 34000, 67),
+    ([(1, 1 + s % 40) for s in range(64)], 261, 261, 4096, (8, 2, 1), 16704, 66),
+    ([(1, 1 + s % 16) for s in range(2000)], 17, 17, 512, (4, 2, 1), 34000, 67),
 ]
 
 
@@ -264,7 +269,7 @@ def _edges(qs):
     # 256 columns: GQA 5, a remainder of one token
     ([(1001, 1333), (97, 97), (1, 700)], 60, 12, "bf16", (8, 2, 1)),
     # the largest batch, and on the split context: 155 KiB of LDS, the most a launch takes
-    ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16", (4, 1, 1)),
+    ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16", (8, 2, 1)),
     ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 3, 1, "bf16", (8, 1, 2)),
 ])
 def test_item_widths(gpu_lib, chunks, hq, hkv, kv, variant):
