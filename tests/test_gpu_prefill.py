@@ -271,6 +271,7 @@ def _edges(qs):
     # the largest batch, and on the split context: 155 KiB of LDS, the most a launch takes
     ([(1, 1 + s % 16) for s in range(4096)], 18, 9, "bf16", (8, 2, 1)),
     ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 3, 1, "bf16", (8, 1, 2)),
+    ([(7, 2100)] + [(1, 1 + s % 16) for s in range(4095)], 5, 5, "bf16", (8, 2, 2)),
 ])
 def test_item_widths(gpu_lib, chunks, hq, hkv, kv, variant):
     """Each width of work item the library chooses between, at the ends of its
